@@ -542,9 +542,21 @@ static __device__ __forceinline__ void wait_vm() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
+// Cache policy of the K/V loads (kAux, the loads' cache-policy bits).  A step
+// reads every retained row once, so the loads of a large launch are streamed
+// (nt): they leave no lines behind in the L2s that each row's one use would
+// have to displace again.  Measured per launch, normal -> nt: a plain read of
+// 470 MB 77.1 -> 68.0 us (6.1 -> 6.9 TB/s, the same over 56 GB read once, so
+// not a matter of what the Infinity Cache keeps), 12 x 300 s with eviction
+// (21 MB) 8.68 -> 8.17 us, dense (78 MB) 19.7 -> 18.3, 28 layers x 12 chunks
+// in one launch (546 MB) 101.0 -> 88.4.  A small launch keeps the normal
+// policy (see stream_rows).
+constexpr int kAuxStream = 2;  // nt
+
 // The 16 direct-to-LDS loads of one pass (8 for K, then 8 for V) into `stage`.
 // pos[j]: in-bounds position of the row whose rank is r0 + 4j + (lane >> 4).
 // ring: compare positions with nr.cur (a constant at every call site).
+template <int kAux>
 static __device__ __forceinline__ void dma_pass(uint8_t *stage, const uint16_t *kbase, const uint16_t *vbase,
                                                 int64_t s_pos, const int32_t (&pos)[8], int lane, bool ring,
                                                 const NewRows &nr) {
@@ -554,14 +566,14 @@ static __device__ __forceinline__ void dma_pass(uint8_t *stage, const uint16_t *
         const int c = sl ^ ((4 * j + q) & 15);
         const uint16_t *kr = kbase + (int64_t)pos[j] * s_pos;
         __builtin_amdgcn_global_load_lds((ring && pos[j] == nr.cur ? nr.k : kr) + 8 * c,
-                                         (lds_void_t *)(stage + j * 1024), 16, 0, 0);
+                                         (lds_void_t *)(stage + j * 1024), 16, 0, kAux);
     }
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         const int c = sl ^ ((4 * j + q) & 15);
         const uint16_t *vr = vbase + (int64_t)pos[j] * s_pos;
         __builtin_amdgcn_global_load_lds((ring && pos[j] == nr.cur ? nr.v : vr) + 8 * c,
-                                         (lds_void_t *)(stage + kTileBytes + j * 1024), 16, 0, 0);
+                                         (lds_void_t *)(stage + kTileBytes + j * 1024), 16, 0, kAux);
     }
 }
 
@@ -626,7 +638,7 @@ static __device__ __forceinline__ bool tab_run(const RangeTab &t, int r0, int va
 // read row p0, as in dma_pos_ranges.  Lane (q, sl) of load j reads chunk
 // sl ^ ((4j + q) & 15) of row 4j + q, as in dma_pass; that chunk's byte
 // offset 16 * (sl ^ q) ^ 64 * (j & 3) repeats with period 4 in j.
-template <bool kFull>
+template <bool kFull, int kAux>
 static __device__ __forceinline__ void dma_pass_run(uint8_t *stage, const uint16_t *kbase, const uint16_t *vbase,
                                                     int64_t s_pos, int p0, int valid, int lane) {
     const int q = lane >> 4, sl = lane & 15;
@@ -643,10 +655,10 @@ static __device__ __forceinline__ void dma_pass_run(uint8_t *stage, const uint16
     }
 #pragma unroll
     for (int j = 0; j < 8; ++j)
-        __builtin_amdgcn_global_load_lds(kb + voff[j], (lds_void_t *)(stage + j * 1024), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds(kb + voff[j], (lds_void_t *)(stage + j * 1024), 16, 0, kAux);
 #pragma unroll
     for (int j = 0; j < 8; ++j)
-        __builtin_amdgcn_global_load_lds(vb + voff[j], (lds_void_t *)(stage + kTileBytes + j * 1024), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds(vb + voff[j], (lds_void_t *)(stage + kTileBytes + j * 1024), 16, 0, kAux);
     // Ends the path with a statement of its own: the compiler would otherwise
     // sink the last load of this and dma_pass's path into one shared block,
     // which takes a 64-bit address.
@@ -657,7 +669,7 @@ static __device__ __forceinline__ void dma_pass_run(uint8_t *stage, const uint16
 // from the range table: consecutive rows through dma_pass_run (tab_run; not
 // for ring storage, whose current row comes from another buffer), else
 // per-row positions through dma_pass.  short_rows: stride_pos < kRunRowLimit.
-template <bool kRing>
+template <bool kRing, int kAux>
 static __device__ __forceinline__ void dma_pass_ranges(uint8_t *stage, const RangeTab &tab, int r0, int r_end,
                                                        int max_len, bool short_rows, const uint16_t *kbase,
                                                        const uint16_t *vbase, int64_t s_pos, int lane, int c4,
@@ -666,13 +678,13 @@ static __device__ __forceinline__ void dma_pass_ranges(uint8_t *stage, const Ran
     int p0;
     if (!kRing && short_rows && tab_run(tab, r0, valid, max_len, p0)) {
         if (valid == kWaveTile)
-            dma_pass_run<true>(stage, kbase, vbase, s_pos, p0, valid, lane);
+            dma_pass_run<true, kAux>(stage, kbase, vbase, s_pos, p0, valid, lane);
         else
-            dma_pass_run<false>(stage, kbase, vbase, s_pos, p0, valid, lane);
+            dma_pass_run<false, kAux>(stage, kbase, vbase, s_pos, p0, valid, lane);
     } else {
         int32_t pos[8];
         dma_pos_ranges(tab, r0, r_end, max_len, c4, pos, bad);
-        dma_pass(stage, kbase, vbase, s_pos, pos, lane, kRing, nr);
+        dma_pass<kAux>(stage, kbase, vbase, s_pos, pos, lane, kRing, nr);
     }
 }
 
@@ -1436,7 +1448,7 @@ static __device__ __forceinline__ void merge_partials(const AttnLaunch &a, int n
 // gap overlap the other's loads.  Index lists are staged too, one pass ahead
 // of the rows.
 // ---------------------------------------------------------------------------
-template <int kSrc, int kStages>
+template <int kSrc, int kStages, int kAux>
 __global__ __launch_bounds__(256) void decode_attn_lds_kernel(const int32_t *__restrict__ src0,
                                                               const int32_t *__restrict__ src1,
                                                               const int32_t *__restrict__ idx,
@@ -1515,12 +1527,12 @@ __global__ __launch_bounds__(256) void decode_attn_lds_kernel(const int32_t *__r
         }
         for (int k = 0;; r += kSplitUnit, ++k) {
             if (kSrc != kSrcIndex) {
-                dma_pass_ranges<kRing>(st[0], tab, r, r_end, a.max_len, short_rows, kbase, vbase, a.s_pos, lane, c4,
+                dma_pass_ranges<kRing, kAux>(st[0], tab, r, r_end, a.max_len, short_rows, kbase, vbase, a.s_pos, lane, c4,
                                        w.bad_pos, nr);
             } else {
                 wait_vm<1>();  // this pass's entries; the next pass's may stay in flight
                 dma_pos_index(ring[k & 1], r, r_end, a.max_len, c4, pos, w.bad_pos);
-                dma_pass(st[0], kbase, vbase, a.s_pos, pos, lane, kRing, nr);
+                dma_pass<kAux>(st[0], kbase, vbase, a.s_pos, pos, lane, kRing, nr);
             }
             wait_vm<0>();
             compute_pass_lds<true>(st[0], qf, min(kWaveTile, r_end - r), a.scale_log2, w, n16, c4);
@@ -1530,26 +1542,26 @@ __global__ __launch_bounds__(256) void decode_attn_lds_kernel(const int32_t *__r
     } else if (r < r_end) {
         int32_t pos[8];
         if (kSrc != kSrcIndex) {
-            dma_pass_ranges<kRing>(st[0], tab, r, r_end, a.max_len, short_rows, kbase, vbase, a.s_pos, lane, c4,
+            dma_pass_ranges<kRing, kAux>(st[0], tab, r, r_end, a.max_len, short_rows, kbase, vbase, a.s_pos, lane, c4,
                                    w.bad_pos, nr);
         } else {
             dma_idx(ring[0], irow, r, lane);
             dma_idx(ring[1], irow, r + kSplitUnit, lane);
             wait_vm<1>();
             dma_pos_index(ring[0], r, r_end, a.max_len, c4, pos, w.bad_pos);
-            dma_pass(st[0], kbase, vbase, a.s_pos, pos, lane, kRing, nr);
+            dma_pass<kAux>(st[0], kbase, vbase, a.s_pos, pos, lane, kRing, nr);
         }
         for (int k = 0;; r += kSplitUnit, ++k) {
             const uint8_t *cur = st[k & 1];
             if (r + kSplitUnit < r_end) {
                 if (kSrc != kSrcIndex) {
-                    dma_pass_ranges<kRing>(st[(k + 1) & 1], tab, r + kSplitUnit, r_end, a.max_len, short_rows, kbase,
+                    dma_pass_ranges<kRing, kAux>(st[(k + 1) & 1], tab, r + kSplitUnit, r_end, a.max_len, short_rows, kbase,
                                            vbase, a.s_pos, lane, c4, w.bad_pos, nr);
                 } else {
                     wait_vm<kStageLoads>();  // entries of the next pass (issued before this pass's rows)
                     dma_pos_index(ring[(k + 1) & 1], r + kSplitUnit, r_end, a.max_len, c4, pos, w.bad_pos);
                     dma_idx(ring[k & 1], irow, r + 2 * kSplitUnit, lane);
-                    dma_pass(st[(k + 1) & 1], kbase, vbase, a.s_pos, pos, lane, kRing, nr);
+                    dma_pass<kAux>(st[(k + 1) & 1], kbase, vbase, a.s_pos, pos, lane, kRing, nr);
                 }
                 if (kSrc != kSrcIndex)
                     wait_vm<kStageLoads>();  // this pass's rows; the next pass's stay in flight
@@ -1845,11 +1857,14 @@ static __device__ __forceinline__ uint32_t div16(uint32_t x, uint32_t magic) { r
 // The WideSched fields are separate scalar arguments (with the pointers, the
 // first 16 dwords, which the build preloads into SGPRs; a struct argument
 // would be loaded from memory first).
-template <int kSrc>
+// kVariant: kSrc, plus kWideCached for the normal cache policy of the K/V loads.
+constexpr int kWideCached = 4;
+template <int kVariant>
 __global__ __launch_bounds__(kWideThreads) void decode_attn_wide_kernel(
     const int32_t *__restrict__ src0, const int32_t *__restrict__ src1, uint32_t xcd, uint32_t magic_n,
     uint32_t len_g, uint32_t hkv_b, uint32_t magic_hkv, uint32_t magic_b,
     const int32_t *__restrict__ idx, const uint16_t *__restrict__ q, const AttnLaunch a) {
+    constexpr int kSrc = kVariant & 3, kAux = (kVariant & kWideCached) ? 0 : kAuxStream;
     const WideSched ws{xcd, magic_n, len_g, hkv_b, magic_hkv, magic_b};
     // G and the policy mode from a preloaded argument: loading them from memory
     // put a second round trip in front of the first K/V loads
@@ -1946,14 +1961,14 @@ __global__ __launch_bounds__(kWideThreads) void decode_attn_wide_kernel(
         u32x4 qf[4];
         load_q(qf, q, row0, G, n16, c4);
         if (kSrc != kSrcIndex) {
-            dma_pass_ranges<kRing>(stage, tab, r0, r_end, a.max_len, short_rows, kbase, vbase, a.s_pos, lane, c4,
+            dma_pass_ranges<kRing, kAux>(stage, tab, r0, r_end, a.max_len, short_rows, kbase, vbase, a.s_pos, lane, c4,
                                    w.bad_pos, nr);
         } else {
             int32_t pos[8];
             dma_idx(&idx_slot[wave][0], irow, r0, lane);
             wait_vm<0>();
             dma_pos_index(&idx_slot[wave][0], r0, r_end, a.max_len, c4, pos, w.bad_pos);
-            dma_pass(stage, kbase, vbase, a.s_pos, pos, lane, kRing, nr);
+            dma_pass<kAux>(stage, kbase, vbase, a.s_pos, pos, lane, kRing, nr);
         }
         if (kSrc == kSrcLayout) layout_ok = layout_valid_late(lw);  // while this pass's rows are on their way
         compute_pass_lds<false, true>(stage, qf, valid, a.scale_log2, w, n16, c4);
@@ -2110,11 +2125,26 @@ static bool small_group_offsets(const AttnLaunch &a) {
     return last < ((__int128)1 << 31);
 }
 
-template <int kSrc>
+// Whether a launch streams its K/V rows past the L2s (see kAuxStream): when a
+// layer's retained rows come to at least kStreamBytes.  Below that, the rows of
+// all layers of a 28-layer decoder (235 MB) fit the 256 MB Infinity Cache, and
+// small ones the 32 MB of L2, so the next token may find them there, and then
+// the normal policy is the faster one.  One cache of 28 layers read again and
+// again, us per launch, normal / streamed: 0.4 MB a layer 4.56 / 5.21, 3.5 MB
+// 5.92 / 6.20, 5.3 MB 6.70 / 7.35, 7.0 MB 6.30 / 6.31, 10.4 MB 6.82 / 6.79,
+// 14 MB 7.33 / 7.18; three caches read in turn, so that less survives: 1.7 MB
+// 5.90 / 6.12, 3.5 MB 6.23 / 6.12, 8.7 MB 6.97 / 6.63, 14 MB 7.65 / 7.21.
+constexpr double kStreamBytes = 8 << 20;
+static bool stream_rows(const AttnLaunch &a) {
+    return (double)a.B * a.Hkv * a.max_keep * (2 * kHeadDim * 2) >= kStreamBytes;
+}
+
+template <int kSrc, int kAux>
 static void launch_decode_attn_mode(const AttnLaunch &a, hipStream_t stream) {
     if (a.wide_wg > 0) {
         const WideSched &w = a.sched;
-        hipLaunchKernelGGL(decode_attn_wide_kernel<kSrc>, dim3((unsigned)a.wide_wg), dim3(kWideThreads), 0, stream,
+        hipLaunchKernelGGL(decode_attn_wide_kernel<kSrc + (kAux == kAuxStream ? 0 : kWideCached)>,
+                           dim3((unsigned)a.wide_wg), dim3(kWideThreads), 0, stream,
                            a.src0, a.src1, w.xcd, w.magic_n,
                            w.len | (uint32_t)(a.pol_per_seq & 3) << 23 | (uint32_t)(a.s_pos < kRunRowLimit) << 25 |
                                (uint32_t)small_group_offsets(a) << 26,
@@ -2128,22 +2158,28 @@ static void launch_decode_attn_mode(const AttnLaunch &a, hipStream_t stream) {
     // compute unit.
     const bool one_round = (int64_t)a.n_split * a.NL * a.Hkv * a.B <= kRoundWorkgroups;
     if (one_round)
-        hipLaunchKernelGGL((decode_attn_lds_kernel<kSrc, 2>), grid, dim3(kWavesPerWg * 64), 0, stream, a.src0, a.src1,
-                           a.idx, a.q, a.max_keep, a.B, a.pol_per_seq, a.Hkv, a.G, a);
+        hipLaunchKernelGGL((decode_attn_lds_kernel<kSrc, 2, kAux>), grid, dim3(kWavesPerWg * 64), 0, stream, a.src0,
+                           a.src1, a.idx, a.q, a.max_keep, a.B, a.pol_per_seq, a.Hkv, a.G, a);
     else
-        hipLaunchKernelGGL((decode_attn_lds_kernel<kSrc, 1>), grid, dim3(kWavesPerWg * 64), 0, stream, a.src0, a.src1,
-                           a.idx, a.q, a.max_keep, a.B, a.pol_per_seq, a.Hkv, a.G, a);
+        hipLaunchKernelGGL((decode_attn_lds_kernel<kSrc, 1, kAux>), grid, dim3(kWavesPerWg * 64), 0, stream, a.src0,
+                           a.src1, a.idx, a.q, a.max_keep, a.B, a.pol_per_seq, a.Hkv, a.G, a);
+}
+
+template <int kSrc>
+static void launch_decode_attn_src(const AttnLaunch &a, hipStream_t stream) {
+    if (stream_rows(a)) launch_decode_attn_mode<kSrc, kAuxStream>(a, stream);
+    else launch_decode_attn_mode<kSrc, 0>(a, stream);
 }
 
 int launch_decode_attn(const AttnLaunch &a, murmur_stream_t stream) {
     if (a.src_mode == kSrcRing)
-        launch_decode_attn_mode<kSrcRing>(a, (hipStream_t)stream);
+        launch_decode_attn_src<kSrcRing>(a, (hipStream_t)stream);
     else if (a.src_mode == kSrcLayout)
-        launch_decode_attn_mode<kSrcLayout>(a, (hipStream_t)stream);
+        launch_decode_attn_src<kSrcLayout>(a, (hipStream_t)stream);
     else if (a.src_mode == kSrcRanges)
-        launch_decode_attn_mode<kSrcRanges>(a, (hipStream_t)stream);
+        launch_decode_attn_src<kSrcRanges>(a, (hipStream_t)stream);
     else
-        launch_decode_attn_mode<kSrcIndex>(a, (hipStream_t)stream);
+        launch_decode_attn_src<kSrcIndex>(a, (hipStream_t)stream);
     return (int)hipGetLastError();
 }
 
