@@ -17,10 +17,12 @@
 // Attention data flow per 64-wide wavefront and pass of 32 retained positions:
 //   K, V rows --global_load_lds_dwordx4--> LDS stage (XOR-swizzled 16 B chunks)
 //   K: ds_read_b128 --> MFMA A operands      S^T = K Q^T (16x16x32 bf16)
-//   V: ds_read_b64_tr_b16 (transposing) --> MFMA B operands
+//   V: ds_read_b64_tr_b16 (transposing) --> MFMA A operands
 //   P = exp2(S - m) stays in registers: the S^T accumulator layout is already
-//   the A-operand layout of O = P V, split into bf16 hi + lo parts so the
-//   product keeps ~16 mantissa bits.
+//   the B-operand layout of O^T = V^T P^T, and each lane's O values belong to
+//   the head whose max and sum it holds, so rescaling them takes no lane
+//   exchange.  P is split into bf16 hi + lo parts so the product keeps ~16
+//   mantissa bits.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -362,8 +364,8 @@ static __device__ __forceinline__ float sum_over_c4(float x) {
 }
 
 // Running softmax state of one wavefront for one (layer, sequence, KV head):
-// lane (head n16, c4) holds the max (log2 units) and sum of head n16; acc holds
-// O rows 4*c4 + i (heads) at head dims 16*db + n16.
+// lane (head n16, c4) holds the max (log2 units) and sum of head n16; acc[db][i]
+// is that head's O at head dim 16*db + 4*c4 + i.
 struct WaveAcc {
     float m_run, l_run;
     f32x4 acc[8];
@@ -448,7 +450,7 @@ static __device__ __forceinline__ void materialize(const T &...x) {
 // Softmax update of one pass from its S^T tile (lane (head n16, c4), register
 // i of block blk: logit of rank 16*blk + 4*c4 + i of the pass): masks ranks
 // at or past `valid`, folds the pass into the running (max, sum) and rescales
-// O, and returns P as the A operand of O = P V in k order (4*c4 + 0..3,
+// O, and returns P as the B operand of O^T = V^T P^T in k order (4*c4 + 0..3,
 // 16 + 4*c4 + 0..3), split into bf16 hi + lo so that hi + lo carries ~16
 // mantissa bits.  kOnline: fold into a running state; otherwise the state is
 // known to be empty.
@@ -469,25 +471,21 @@ static __device__ __forceinline__ void softmax_step(const f32x4 (&s)[2], int val
                        fmaxf(fmaxf(x[1][0], x[1][1]), fmaxf(x[1][2], x[1][3])));
     tmax = max_over_c4(tmax);
     const float m_new = kOnline ? fmaxf(w.m_run, tmax) : tmax;  // finite: rank 0 of the pass is valid
-    float psum = 0.f;
     float pr[2][4];
 #pragma unroll
     for (int blk = 0; blk < 2; ++blk)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            pr[blk][i] = __builtin_amdgcn_exp2f(x[blk][i] - m_new);  // in [0, 1]
-            psum += pr[blk][i];
-        }
-    psum = sum_over_c4(psum);
+        for (int i = 0; i < 4; ++i) pr[blk][i] = __builtin_amdgcn_exp2f(x[blk][i] - m_new);  // in [0, 1]
+    const float psum = sum_over_c4(((pr[0][0] + pr[0][1]) + (pr[0][2] + pr[0][3])) +
+                                   ((pr[1][0] + pr[1][1]) + (pr[1][2] + pr[1][3])));
     if (kOnline) {
         const float alpha = __builtin_amdgcn_exp2f(w.m_run - m_new);  // 0 while the state is empty
         w.l_run = w.l_run * alpha + psum;
-        // Rescale O rows: row 4*c4 + i belongs to head 4*c4 + i.
+        // A lane's O values belong to its own head.  Most passes raise no head's max
+        // (alpha is 1 in every lane).
+        if (__ballot(alpha != 1.f)) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float ai = __shfl(alpha, 4 * c4 + i);
-#pragma unroll
-            for (int db = 0; db < 8; ++db) w.acc[db][i] *= ai;
+            for (int db = 0; db < 8; ++db) w.acc[db] *= alpha;
         }
     } else {
         w.l_run = psum;
@@ -718,7 +716,7 @@ static __device__ __forceinline__ void dma_pos_index(const uint8_t *slot, int r0
 }
 
 // One pass from an LDS stage: operand reads, S^T = K Q^T, softmax update,
-// O += P V.  kWaitDma: the stage's direct-to-LDS loads (dma_pass: the K tile's,
+// O^T += V^T P^T.  kWaitDma: the stage's direct-to-LDS loads (dma_pass: the K tile's,
 // then the V tile's, the last loads this wavefront issued) may still be in
 // flight; the K operands are read once the K loads are in, and S^T and the
 // softmax are computed while the V loads land.
@@ -827,13 +825,13 @@ static __device__ __forceinline__ void compute_pass_lds(const uint8_t *stage, co
             : "v"(va[0]), "v"(va[1]), "v"(va[2]), "v"(va[3]), "v"(va[4]), "v"(va[5]), "v"(va[6]), "v"(va[7])
             : "memory");
     }
-    // B operand of head dims 16*db .. +15: positions 4*c4 .. +3 (h = 0) and
-    // 16 + 4*c4 .. +3 (h = 1), the k order of P.
+    // The transposing reads give lane n16 head dim 16*db + n16 of positions
+    // 4*c4 .. +3 (h = 0) and 16 + 4*c4 .. +3 (h = 1), the k order of P.
 #pragma unroll
     for (int db = 0; db < 8; ++db) {
-        const u32x4 bv = u32x4{vf[2 * db][0], vf[2 * db][1], vf[2 * db + 1][0], vf[2 * db + 1][1]};
-        w.acc[db] = mfma16x16x32(p_hi, bv, w.acc[db]);
-        w.acc[db] = mfma16x16x32(p_lo, bv, w.acc[db]);
+        const u32x4 av = u32x4{vf[2 * db][0], vf[2 * db][1], vf[2 * db + 1][0], vf[2 * db + 1][1]};
+        w.acc[db] = mfma16x16x32(av, p_hi, w.acc[db]);
+        w.acc[db] = mfma16x16x32(av, p_lo, w.acc[db]);
     }
 }
 
@@ -1107,9 +1105,8 @@ static __device__ __forceinline__ void publish_wave(const WaveAcc &w, float *o_w
         cl.ml[n16][wave][1] = w.l_run;
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int db = 0; db < 8; ++db) o_w[(4 * c4 + i) * kOStride + 16 * db + n16] = w.acc[db][i];
+    for (int db = 0; db < 8; ++db)
+        *reinterpret_cast<f32x4 *>(&o_w[n16 * kOStride + 16 * db + 4 * c4]) = w.acc[db];
 }
 
 // The workgroup's state of head h, head dims d0 .. d0+3, from the published
@@ -1879,8 +1876,6 @@ __global__ __launch_bounds__(kWideThreads) void decode_attn_wide_kernel(
     __shared__ CombineLdsT<kWideWaves> cl;
     __shared__ int s_last;
     __shared__ int s_wave_flag[kWideWaves];
-    static_assert(kMaxMergeSplits * kMaxGroup * 2 * 4 <= sizeof(stages) && kMaxGroup * kOStride * 4 <= kStageBytes,
-                  "merge scratch and published rows fit the stages");
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -1983,7 +1978,6 @@ __global__ __launch_bounds__(kWideThreads) void decode_attn_wide_kernel(
         w.bad_pos = 0;
     }
     const bool bad_count = cnt_seq < 1 || cnt_seq > max_keep;
-
     if (kRing) store_new_row(a, app, nr, kbase, vbase, lane);
     float *o_lds = reinterpret_cast<float *>(&stages[0][0]);  // each wavefront's O rows in its own stage
     constexpr int kStageFloats = kStageBytes / 4;
