@@ -664,9 +664,11 @@ static __device__ __forceinline__ void dma_pass_run(uint8_t *stage, const uint16
 }
 
 // The 16 K/V loads of the pass at ranks r0 .. min(r0 + kWaveTile, r_end) - 1
-// from the range table: consecutive rows through dma_pass_run (tab_run; not
-// for ring storage, whose current row comes from another buffer), else
-// per-row positions through dma_pass.  short_rows: stride_pos < kRunRowLimit.
+// from the range table: consecutive rows through dma_pass_run (tab_run; in
+// ring storage, passes that hold the current row, which comes from another
+// buffer, are left out: one pass in a sequence's retained set, where taking
+// them all per row cost 0.3 us on 12 x 300 s), else per-row positions through
+// dma_pass.  short_rows: stride_pos < kRunRowLimit.
 template <bool kRing, int kAux>
 static __device__ __forceinline__ void dma_pass_ranges(uint8_t *stage, const RangeTab &tab, int r0, int r_end,
                                                        int max_len, bool short_rows, const uint16_t *kbase,
@@ -674,7 +676,8 @@ static __device__ __forceinline__ void dma_pass_ranges(uint8_t *stage, const Ran
                                                        int &bad, const NewRows &nr) {
     const int valid = min(kWaveTile, r_end - r0);
     int p0;
-    if (!kRing && short_rows && tab_run(tab, r0, valid, max_len, p0)) {
+    if (short_rows && tab_run(tab, r0, valid, max_len, p0) &&
+        (!kRing || (uint32_t)(nr.cur - p0) >= (uint32_t)valid)) {
         if (valid == kWaveTile)
             dma_pass_run<true, kAux>(stage, kbase, vbase, s_pos, p0, valid, lane);
         else
@@ -1900,6 +1903,7 @@ __global__ __launch_bounds__(kWideThreads) void decode_attn_wide_kernel(
     int policy_bad = 0;
     int32_t cur_row = -1;  // ring storage: the current token's row
     const int32_t seq_w = seq_words<kSrc>(src0, src1, b, pol_per_seq, layer, B);
+    if (kSrc == kSrcIndex) __builtin_amdgcn_sched_barrier(0);  // the count's load stays ahead of the scalar wait below
     // Every launch field the kernel reads, pinned in scalar registers here: their
     // loads go out in one batch ahead of one wait, which the vector load above
     // overlaps, instead of later batches whose waits would each add a round trip
@@ -1908,6 +1912,16 @@ __global__ __launch_bounds__(kWideThreads) void decode_attn_wide_kernel(
                 a.ticket, a.part_ml, a.part_o, a.part_ml_bytes, a.part_o_bytes, a.out_f32);
     if (kSrc == kSrcLayout || kSrc == kSrcRing) materialize(a.idx_out, a.count_out, a.ranges_out);
     if (kSrc == kSrcRing) materialize(a.ring_cap, a.k_new, a.v_new);
+    // Index lists: this pass's entries, before the count arrives (their ranks do
+    // not depend on it, and the list has max_keep of them whatever the count):
+    // behind the count they were a second round trip in front of the first K/V
+    // load.
+    __amdgpu_buffer_rsrc_t irow;
+    const int r_first = (int)(split * len) + wave * kWaveTile;
+    if (kSrc == kSrcIndex) {
+        irow = raw_buffer(idx + (int64_t)b * max_keep, (uint32_t)max_keep * 4u);  // ranks past the list read as zeros
+        dma_idx(&idx_slot[wave][0], irow, r_first, lane);
+    }
     int32_t lw[9];  // kSrcLayout: the layout and policy words, tested once the first loads are out
     int cnt_seq = seq_count_from<kSrc>(seq_w, a.ring_cap, rg, policy_bad, cur_row, lw);
     const int cnt = cnt_seq < 0 ? 0 : (cnt_seq > max_keep ? max_keep : cnt_seq);
@@ -1915,9 +1929,7 @@ __global__ __launch_bounds__(kWideThreads) void decode_attn_wide_kernel(
     const int r_end = min(r_begin + (int)len, cnt);
 
     RangeTab tab;
-    __amdgpu_buffer_rsrc_t irow;
     if (kSrc != kSrcIndex) tab = make_tab(rg);
-    else irow = raw_buffer(idx + (int64_t)b * max_keep, (uint32_t)max_keep * 4u);  // ranks past the count are masked
 
     const int64_t row0 = (int64_t)lb * (Hkv * G) + g * G;  // first output row of the group
     // The group's first K/V element: in 32-bit arithmetic when the launch found
@@ -1942,7 +1954,7 @@ __global__ __launch_bounds__(kWideThreads) void decode_attn_wide_kernel(
 
     WaveAcc w;
     wave_acc_reset(w);
-    const int r0 = r_begin + wave * kWaveTile;
+    const int r0 = r_first;
     bool layout_ok = true;
     materialize(kbase, vbase, a.s_pos, a.max_len, a.scale_log2, cnt);
     if (kRing) materialize(nr.k, nr.v, nr.cur);
@@ -1960,8 +1972,7 @@ __global__ __launch_bounds__(kWideThreads) void decode_attn_wide_kernel(
                                    w.bad_pos, nr);
         } else {
             int32_t pos[8];
-            dma_idx(&idx_slot[wave][0], irow, r0, lane);
-            wait_vm<0>();
+            wait_vm<0>();  // the entries
             dma_pos_index(&idx_slot[wave][0], r0, r_end, a.max_len, c4, pos, w.bad_pos);
             dma_pass<kAux>(stage, kbase, vbase, a.s_pos, pos, lane, kRing, nr);
         }
