@@ -293,7 +293,7 @@ int murmur_decode_attn_workspace_init(void *ws_dev, size_t ws_bytes, murmur_stre
  *   scale:      logit scale (1/sqrt(D) for unscaled queries), finite;
  *   split_len:  the work schedule.  A positive multiple of 32: each (layer,
  *               sequence, KV head) is cut into splits of that many retained
- *               positions, one workgroup each (its four wavefronts take
+ *               positions, one workgroup each (its wavefronts take
  *               passes of 32 positions in turn), merged by log-sum-exp.
  *               0: automatic split length (at most one dispatch round of
  *               workgroups when the work is small, at most 64 splits per

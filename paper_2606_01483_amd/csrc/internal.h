@@ -12,8 +12,7 @@ namespace murmur {
 constexpr int kHeadDim = 128;     // head_dim supported by the attention kernel
 constexpr int kMaxGroup = 16;     // query heads per KV head (MFMA tile height)
 constexpr int kWaveTile = 32;     // retained positions one wavefront handles per pass
-constexpr int kWavesPerWg = 4;
-constexpr int kSplitUnit = kWaveTile * kWavesPerWg;  // 128 positions: one pass of a workgroup
+constexpr int kSplitUnit = 4 * kWaveTile;  // the LDS-staged schedule's split counts are chosen in units of 128 positions
 constexpr int kMaxAutoSplits = 64;
 constexpr int kRoundWorkgroups = 256;     // one workgroup per compute unit
 // Splits one merge can combine: it stages 2 * n_split * G + 2 * G floats in

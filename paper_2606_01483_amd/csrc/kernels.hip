@@ -718,14 +718,13 @@ static __device__ __forceinline__ void dma_pos_index(const uint8_t *slot, int r0
     }
 }
 
-// One pass from an LDS stage: operand reads, S^T = K Q^T, softmax update,
-// O^T += V^T P^T.  kWaitDma: the stage's direct-to-LDS loads (dma_pass: the K tile's,
-// then the V tile's, the last loads this wavefront issued) may still be in
-// flight; the K operands are read once the K loads are in, and S^T and the
-// softmax are computed while the V loads land.
-template <bool kOnline, bool kWaitDma = false>
-static __device__ __forceinline__ void compute_pass_lds(const uint8_t *stage, const u32x4 (&qf)[4], int valid,
-                                                        float scale_log2, WaveAcc &w, int n16, int c4) {
+// The one pass of a wavefront of the wide kernel, from its LDS stage: operand
+// reads, S^T = K Q^T, softmax, O^T = V^T P^T.  The stage's direct-to-LDS loads
+// (dma_pass: the K tile's, then the V tile's, the last loads this wavefront
+// issued) may still be in flight: the K operands are read once the K loads are
+// in, and S^T and the softmax are computed while the V loads land.
+static __device__ __forceinline__ void compute_pass_wide(const uint8_t *stage, const u32x4 (&qf)[4], int valid,
+                                                         float scale_log2, WaveAcc &w, int n16, int c4) {
     const uint32_t kt = lds_addr(stage), vt = kt + kTileBytes;
     // K operand (blk, kc): row 16*blk + n16, chunk 4*kc + c4 (row & 15 == n16);
     // blk 1 is 16 rows (4096 bytes) further.
@@ -742,57 +741,21 @@ static __device__ __forceinline__ void compute_pass_lds(const uint8_t *stage, co
         va[db] = vt + vr * kTileRowBytes + (((2 * db + ((n16 & 3) >> 1)) ^ vr) << 4) + (n16 & 1) * 8;
     u32x4 kf[8];
     u32x2 vf[16];
-    if constexpr (!kWaitDma) {
-        asm volatile(
-            "ds_read_b128 %0, %24\n\t"
-            "ds_read_b128 %1, %25\n\t"
-            "ds_read_b128 %2, %26\n\t"
-            "ds_read_b128 %3, %27\n\t"
-            "ds_read_b128 %4, %24 offset:4096\n\t"
-            "ds_read_b128 %5, %25 offset:4096\n\t"
-            "ds_read_b128 %6, %26 offset:4096\n\t"
-            "ds_read_b128 %7, %27 offset:4096\n\t"
-            "ds_read_b64_tr_b16 %8, %28\n\t"
-            "ds_read_b64_tr_b16 %9, %28 offset:4096\n\t"
-            "ds_read_b64_tr_b16 %10, %29\n\t"
-            "ds_read_b64_tr_b16 %11, %29 offset:4096\n\t"
-            "ds_read_b64_tr_b16 %12, %30\n\t"
-            "ds_read_b64_tr_b16 %13, %30 offset:4096\n\t"
-            "ds_read_b64_tr_b16 %14, %31\n\t"
-            "ds_read_b64_tr_b16 %15, %31 offset:4096\n\t"
-            "ds_read_b64_tr_b16 %16, %32\n\t"
-            "ds_read_b64_tr_b16 %17, %32 offset:4096\n\t"
-            "ds_read_b64_tr_b16 %18, %33\n\t"
-            "ds_read_b64_tr_b16 %19, %33 offset:4096\n\t"
-            "ds_read_b64_tr_b16 %20, %34\n\t"
-            "ds_read_b64_tr_b16 %21, %34 offset:4096\n\t"
-            "ds_read_b64_tr_b16 %22, %35\n\t"
-            "ds_read_b64_tr_b16 %23, %35 offset:4096\n\t"
-            "s_waitcnt lgkmcnt(0)"
-            : "=&v"(kf[0]), "=&v"(kf[1]), "=&v"(kf[2]), "=&v"(kf[3]), "=&v"(kf[4]), "=&v"(kf[5]), "=&v"(kf[6]), "=&v"(kf[7]),
-              "=&v"(vf[0]), "=&v"(vf[1]), "=&v"(vf[2]), "=&v"(vf[3]), "=&v"(vf[4]), "=&v"(vf[5]), "=&v"(vf[6]), "=&v"(vf[7]),
-              "=&v"(vf[8]), "=&v"(vf[9]), "=&v"(vf[10]), "=&v"(vf[11]), "=&v"(vf[12]), "=&v"(vf[13]), "=&v"(vf[14]),
-              "=&v"(vf[15])
-            : "v"(ka[0]), "v"(ka[1]), "v"(ka[2]), "v"(ka[3]), "v"(va[0]), "v"(va[1]), "v"(va[2]), "v"(va[3]), "v"(va[4]),
-              "v"(va[5]), "v"(va[6]), "v"(va[7])
-            : "memory");
-    } else {
-        wait_vm<kStageLoads / 2>();  // the K tile's loads (issued before the V tile's)
-        asm volatile(
-            "ds_read_b128 %0, %8\n\t"
-            "ds_read_b128 %1, %9\n\t"
-            "ds_read_b128 %2, %10\n\t"
-            "ds_read_b128 %3, %11\n\t"
-            "ds_read_b128 %4, %8 offset:4096\n\t"
-            "ds_read_b128 %5, %9 offset:4096\n\t"
-            "ds_read_b128 %6, %10 offset:4096\n\t"
-            "ds_read_b128 %7, %11 offset:4096\n\t"
-            "s_waitcnt lgkmcnt(0)"
-            : "=&v"(kf[0]), "=&v"(kf[1]), "=&v"(kf[2]), "=&v"(kf[3]), "=&v"(kf[4]), "=&v"(kf[5]), "=&v"(kf[6]),
-              "=&v"(kf[7])
-            : "v"(ka[0]), "v"(ka[1]), "v"(ka[2]), "v"(ka[3])
-            : "memory");
-    }
+    wait_vm<kStageLoads / 2>();  // the K tile's loads (issued before the V tile's)
+    asm volatile(
+        "ds_read_b128 %0, %8\n\t"
+        "ds_read_b128 %1, %9\n\t"
+        "ds_read_b128 %2, %10\n\t"
+        "ds_read_b128 %3, %11\n\t"
+        "ds_read_b128 %4, %8 offset:4096\n\t"
+        "ds_read_b128 %5, %9 offset:4096\n\t"
+        "ds_read_b128 %6, %10 offset:4096\n\t"
+        "ds_read_b128 %7, %11 offset:4096\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(kf[0]), "=&v"(kf[1]), "=&v"(kf[2]), "=&v"(kf[3]), "=&v"(kf[4]), "=&v"(kf[5]), "=&v"(kf[6]),
+          "=&v"(kf[7])
+        : "v"(ka[0]), "v"(ka[1]), "v"(ka[2]), "v"(ka[3])
+        : "memory");
     f32x4 s[2];
 #pragma unroll
     for (int blk = 0; blk < 2; ++blk) {
@@ -801,38 +764,108 @@ static __device__ __forceinline__ void compute_pass_lds(const uint8_t *stage, co
         for (int kc = 0; kc < 4; ++kc) s[blk] = mfma16x16x32(kf[4 * blk + kc], qf[kc], s[blk]);
     }
     u32x4 p_hi, p_lo;
-    softmax_step<kOnline>(s, valid, scale_log2, w, c4, p_hi, p_lo);
-    if constexpr (kWaitDma) {
-        wait_vm<0>();  // the V tile's loads
-        asm volatile(
-            "ds_read_b64_tr_b16 %0, %16\n\t"
-            "ds_read_b64_tr_b16 %1, %16 offset:4096\n\t"
-            "ds_read_b64_tr_b16 %2, %17\n\t"
-            "ds_read_b64_tr_b16 %3, %17 offset:4096\n\t"
-            "ds_read_b64_tr_b16 %4, %18\n\t"
-            "ds_read_b64_tr_b16 %5, %18 offset:4096\n\t"
-            "ds_read_b64_tr_b16 %6, %19\n\t"
-            "ds_read_b64_tr_b16 %7, %19 offset:4096\n\t"
-            "ds_read_b64_tr_b16 %8, %20\n\t"
-            "ds_read_b64_tr_b16 %9, %20 offset:4096\n\t"
-            "ds_read_b64_tr_b16 %10, %21\n\t"
-            "ds_read_b64_tr_b16 %11, %21 offset:4096\n\t"
-            "ds_read_b64_tr_b16 %12, %22\n\t"
-            "ds_read_b64_tr_b16 %13, %22 offset:4096\n\t"
-            "ds_read_b64_tr_b16 %14, %23\n\t"
-            "ds_read_b64_tr_b16 %15, %23 offset:4096\n\t"
-            "s_waitcnt lgkmcnt(0)"
-            : "=&v"(vf[0]), "=&v"(vf[1]), "=&v"(vf[2]), "=&v"(vf[3]), "=&v"(vf[4]), "=&v"(vf[5]), "=&v"(vf[6]),
-              "=&v"(vf[7]), "=&v"(vf[8]), "=&v"(vf[9]), "=&v"(vf[10]), "=&v"(vf[11]), "=&v"(vf[12]), "=&v"(vf[13]),
-              "=&v"(vf[14]), "=&v"(vf[15])
-            : "v"(va[0]), "v"(va[1]), "v"(va[2]), "v"(va[3]), "v"(va[4]), "v"(va[5]), "v"(va[6]), "v"(va[7])
-            : "memory");
-    }
+    softmax_step<false>(s, valid, scale_log2, w, c4, p_hi, p_lo);
+    wait_vm<0>();  // the V tile's loads
+    asm volatile(
+        "ds_read_b64_tr_b16 %0, %16\n\t"
+        "ds_read_b64_tr_b16 %1, %16 offset:4096\n\t"
+        "ds_read_b64_tr_b16 %2, %17\n\t"
+        "ds_read_b64_tr_b16 %3, %17 offset:4096\n\t"
+        "ds_read_b64_tr_b16 %4, %18\n\t"
+        "ds_read_b64_tr_b16 %5, %18 offset:4096\n\t"
+        "ds_read_b64_tr_b16 %6, %19\n\t"
+        "ds_read_b64_tr_b16 %7, %19 offset:4096\n\t"
+        "ds_read_b64_tr_b16 %8, %20\n\t"
+        "ds_read_b64_tr_b16 %9, %20 offset:4096\n\t"
+        "ds_read_b64_tr_b16 %10, %21\n\t"
+        "ds_read_b64_tr_b16 %11, %21 offset:4096\n\t"
+        "ds_read_b64_tr_b16 %12, %22\n\t"
+        "ds_read_b64_tr_b16 %13, %22 offset:4096\n\t"
+        "ds_read_b64_tr_b16 %14, %23\n\t"
+        "ds_read_b64_tr_b16 %15, %23 offset:4096\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(vf[0]), "=&v"(vf[1]), "=&v"(vf[2]), "=&v"(vf[3]), "=&v"(vf[4]), "=&v"(vf[5]), "=&v"(vf[6]),
+          "=&v"(vf[7]), "=&v"(vf[8]), "=&v"(vf[9]), "=&v"(vf[10]), "=&v"(vf[11]), "=&v"(vf[12]), "=&v"(vf[13]),
+          "=&v"(vf[14]), "=&v"(vf[15])
+        : "v"(va[0]), "v"(va[1]), "v"(va[2]), "v"(va[3]), "v"(va[4]), "v"(va[5]), "v"(va[6]), "v"(va[7])
+        : "memory");
     // The transposing reads give lane n16 head dim 16*db + n16 of positions
     // 4*c4 .. +3 (h = 0) and 16 + 4*c4 .. +3 (h = 1), the k order of P.
 #pragma unroll
     for (int db = 0; db < 8; ++db) {
         const u32x4 av = u32x4{vf[2 * db][0], vf[2 * db][1], vf[2 * db + 1][0], vf[2 * db + 1][1]};
+        w.acc[db] = mfma16x16x32(av, p_hi, w.acc[db]);
+        w.acc[db] = mfma16x16x32(av, p_lo, w.acc[db]);
+    }
+}
+
+// A pass of the LDS-staged kernel: read_operands takes the K and V operands of a
+// stage whose loads have landed into registers, so that the stage can take the
+// next pass's loads before this one is computed; compute_operands then does
+// S^T = K Q^T, the softmax update of the running state and O^T += V^T P^T.
+struct PassOperands {
+    u32x4 kf[8];
+    u32x2 vf[16];
+};
+static __device__ __forceinline__ void read_operands(PassOperands &ops, const uint8_t *stage, int n16, int c4) {
+    const uint32_t kt = lds_addr(stage), vt = kt + kTileBytes;
+    uint32_t ka[4], va[8];
+#pragma unroll
+    for (int kc = 0; kc < 4; ++kc) ka[kc] = kt + n16 * kTileRowBytes + (((4 * kc + c4) ^ n16) << 4);
+    const int vr = 4 * c4 + (n16 >> 2);
+#pragma unroll
+    for (int db = 0; db < 8; ++db)
+        va[db] = vt + vr * kTileRowBytes + (((2 * db + ((n16 & 3) >> 1)) ^ vr) << 4) + (n16 & 1) * 8;
+    u32x4 (&kf)[8] = ops.kf;
+    u32x2 (&vf)[16] = ops.vf;
+    asm volatile(
+        "ds_read_b128 %0, %24\n\t"
+        "ds_read_b128 %1, %25\n\t"
+        "ds_read_b128 %2, %26\n\t"
+        "ds_read_b128 %3, %27\n\t"
+        "ds_read_b128 %4, %24 offset:4096\n\t"
+        "ds_read_b128 %5, %25 offset:4096\n\t"
+        "ds_read_b128 %6, %26 offset:4096\n\t"
+        "ds_read_b128 %7, %27 offset:4096\n\t"
+        "ds_read_b64_tr_b16 %8, %28\n\t"
+        "ds_read_b64_tr_b16 %9, %28 offset:4096\n\t"
+        "ds_read_b64_tr_b16 %10, %29\n\t"
+        "ds_read_b64_tr_b16 %11, %29 offset:4096\n\t"
+        "ds_read_b64_tr_b16 %12, %30\n\t"
+        "ds_read_b64_tr_b16 %13, %30 offset:4096\n\t"
+        "ds_read_b64_tr_b16 %14, %31\n\t"
+        "ds_read_b64_tr_b16 %15, %31 offset:4096\n\t"
+        "ds_read_b64_tr_b16 %16, %32\n\t"
+        "ds_read_b64_tr_b16 %17, %32 offset:4096\n\t"
+        "ds_read_b64_tr_b16 %18, %33\n\t"
+        "ds_read_b64_tr_b16 %19, %33 offset:4096\n\t"
+        "ds_read_b64_tr_b16 %20, %34\n\t"
+        "ds_read_b64_tr_b16 %21, %34 offset:4096\n\t"
+        "ds_read_b64_tr_b16 %22, %35\n\t"
+        "ds_read_b64_tr_b16 %23, %35 offset:4096\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(kf[0]), "=&v"(kf[1]), "=&v"(kf[2]), "=&v"(kf[3]), "=&v"(kf[4]), "=&v"(kf[5]), "=&v"(kf[6]), "=&v"(kf[7]),
+          "=&v"(vf[0]), "=&v"(vf[1]), "=&v"(vf[2]), "=&v"(vf[3]), "=&v"(vf[4]), "=&v"(vf[5]), "=&v"(vf[6]), "=&v"(vf[7]),
+          "=&v"(vf[8]), "=&v"(vf[9]), "=&v"(vf[10]), "=&v"(vf[11]), "=&v"(vf[12]), "=&v"(vf[13]), "=&v"(vf[14]),
+          "=&v"(vf[15])
+        : "v"(ka[0]), "v"(ka[1]), "v"(ka[2]), "v"(ka[3]), "v"(va[0]), "v"(va[1]), "v"(va[2]), "v"(va[3]), "v"(va[4]),
+          "v"(va[5]), "v"(va[6]), "v"(va[7])
+        : "memory");
+}
+static __device__ __forceinline__ void compute_operands(const PassOperands &ops, const u32x4 (&qf)[4], int valid,
+                                                        float scale_log2, WaveAcc &w, int c4) {
+    f32x4 s[2];
+#pragma unroll
+    for (int blk = 0; blk < 2; ++blk) {
+        s[blk] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kc = 0; kc < 4; ++kc) s[blk] = mfma16x16x32(ops.kf[4 * blk + kc], qf[kc], s[blk]);
+    }
+    u32x4 p_hi, p_lo;
+    softmax_step<true>(s, valid, scale_log2, w, c4, p_hi, p_lo);
+#pragma unroll
+    for (int db = 0; db < 8; ++db) {
+        const u32x4 av = u32x4{ops.vf[2 * db][0], ops.vf[2 * db][1], ops.vf[2 * db + 1][0], ops.vf[2 * db + 1][1]};
         w.acc[db] = mfma16x16x32(av, p_hi, w.acc[db]);
         w.acc[db] = mfma16x16x32(av, p_lo, w.acc[db]);
     }
@@ -1087,16 +1120,15 @@ static __device__ __forceinline__ int barrier_or(int flag, int *s_wave_flag, int
     return r;
 }
 
-// Combine of a workgroup's four wavefronts.  Each wavefront publishes its
+// Combine of a workgroup's wavefronts.  Each wavefront publishes its
 // state -- (max, sum) per head and its unscaled O rows -- into LDS regions no
 // other wavefront touches before the workgroup barrier that follows; after
-// the barrier the threads writing the result rescale and add the four states
+// the barrier the threads writing the result rescale and add the states
 // as they read them.  One barrier and no dependent LDS round trip between.
 template <int kWaves>
 struct __attribute__((aligned(16))) CombineLdsT {
     float ml[kMaxGroup][kWaves][2];  // per head and wavefront: max (log2 units), sum
 };
-using CombineLds = CombineLdsT<kWavesPerWg>;
 constexpr int kOStride = kHeadDim + 4;                  // floats per published O row (padded: conflict-free stores)
 constexpr int kOWaveBytes = kMaxGroup * kOStride * 4;   // 8448: a wavefront's published rows
 
@@ -1437,30 +1469,38 @@ static __device__ __forceinline__ void merge_partials(const AttnLaunch &a, int n
 
 // ---------------------------------------------------------------------------
 // decode_attn, split schedule with LDS-staged passes, for splits longer than
-// the wide schedule's: one workgroup of four wavefronts per (split, layer and
-// KV head, sequence), wavefront w taking passes w, w + 4, ...  With
-// kStages = 2 each wavefront double-buffers its passes in two LDS stages (K
-// and V, 16 KiB per stage), issuing the next pass's direct-to-LDS loads before
-// computing the current one; the workgroup takes 128 KiB of LDS, a compute
-// unit to itself.  With kStages = 1 (grids of more than one dispatch round)
-// each wavefront loads a pass, waits and computes it: 64 KiB, so two
-// workgroups share a compute unit and one's prologue, epilogue and dispatch
-// gap overlap the other's loads.  Index lists are staged too, one pass ahead
-// of the rows.
+// the wide schedule's: one workgroup of kWaves wavefronts per (split, layer and
+// KV head, sequence), wavefront w taking passes w, w + kWaves, ...  Each
+// wavefront has one LDS stage (K and V, 16 KiB): once a pass's rows have landed
+// it reads the operands into registers, starts the next pass's direct-to-LDS
+// loads into the same stage and then computes, so loads are in flight all the
+// time.  What a compute unit does besides loading is bound by instruction
+// issue (a wavefront issues one per 4 cycles, a dependent one per 8: 1.2-1.5 us
+// for a pass, 0.7-1.1 us for its loads), so two wavefronts per SIMD share it:
+// with kWaves = 8 the workgroup takes a compute unit to itself (128 KiB; four
+// wavefronts with two stages each, one per SIMD, took 18.2 us on 12 x 300 s
+// dense and 16.4 us on 16 chunks from range tables, 17.7 and 15.4 now), and with
+// kWaves = 4 (64 KiB, grids of more than one dispatch round) two workgroups do,
+// one's prologue, epilogue and dispatch gap overlapping the other's loads.
+// Index lists are staged too, one pass ahead of the rows.
+//
+// A sequence has as many splits as its own count needs; workgroups past them
+// leave at once, and a sequence of one split stores its output without a merge.
 // ---------------------------------------------------------------------------
-template <int kSrc, int kStages, int kAux>
-__global__ __launch_bounds__(256) void decode_attn_lds_kernel(const int32_t *__restrict__ src0,
+template <int kSrc, int kWaves, int kAux>
+__global__ __launch_bounds__(kWaves * 64, 2) void decode_attn_lds_kernel(const int32_t *__restrict__ src0,
                                                               const int32_t *__restrict__ src1,
                                                               const int32_t *__restrict__ idx,
                                                               const uint16_t *__restrict__ q, int32_t max_keep,
                                                               int32_t B, int32_t pol_per_seq, int32_t Hkv, int32_t G,
                                                           const AttnLaunch a) {
-    __shared__ __attribute__((aligned(16))) uint8_t stages[kWavesPerWg][kStages][kStageBytes];
-    __shared__ __attribute__((aligned(16))) uint8_t idx_ring[kSrc != kSrcIndex ? 1 : kWavesPerWg][2][kIdxSlotBytes];
-    __shared__ CombineLds cl;
+    __shared__ __attribute__((aligned(16))) uint8_t stages[kWaves][kStageBytes];
+    __shared__ __attribute__((aligned(16))) uint8_t idx_ring[kSrc != kSrcIndex ? 1 : kWaves][2][kIdxSlotBytes];
+    __shared__ CombineLdsT<kWaves> cl;
     __shared__ int s_last;
-    __shared__ int s_wave_flag[kWavesPerWg];
-    static_assert(kMaxMergeSplits * kMaxGroup * 2 * 4 <= sizeof(stages) && kOWaveBytes <= kStages * kStageBytes,
+    __shared__ int s_wave_flag[kWaves];
+    constexpr int kUnit = kWaves * kWaveTile;  // ranks of one pass of every wavefront
+    static_assert(kMaxMergeSplits * kMaxGroup * 2 * 4 <= sizeof(stages) && kOWaveBytes <= kStageBytes,
                   "merge scratch and published rows fit the stages");
 
     const int tid = threadIdx.x;
@@ -1469,23 +1509,26 @@ __global__ __launch_bounds__(256) void decode_attn_lds_kernel(const int32_t *__r
     const int n16 = lane & 15;
     const int c4 = lane >> 4;
 
-    // Grid: x = split, y = layer * Hkv + KV head, z = sequence.  The
-    // sequence's retained-set description is loaded first: the first K/V loads
-    // wait for it and for nothing else.
-    const int split = blockIdx.x;
-    const int b = blockIdx.z;
+    // Grid: x = layer * Hkv + KV head, y = sequence, z = split.  The splits
+    // that shorter sequences do not have come last: consecutive workgroups go to
+    // consecutive XCDs, and as the fastest dimension they would leave some XCDs
+    // without work.  The sequence's retained-set description is loaded first: the
+    // first K/V loads wait for it and for nothing else.
+    const int split = blockIdx.z;
+    const int b = blockIdx.y;
     int32_t rg[2 * kPieces];
     int policy_bad = 0;
     int32_t cur_row = -1;  // ring storage: the current token's row
-    const int layer = (int)blockIdx.y / Hkv;
+    const int layer = (int)blockIdx.x / Hkv;
     const int cnt_seq = seq_count_scalar<kSrc>(src0, src1, b, pol_per_seq, layer, B, a.ring_cap, rg, policy_bad, cur_row);
-    const int g = (int)blockIdx.y - layer * Hkv;
+    const int g = (int)blockIdx.x - layer * Hkv;
     const int lb = layer * B + b;
     const int grp = lb * Hkv + g;  // ((layer * B) + b) * Hkv + g
     const int Hq = Hkv * G;
     const bool bad_count = cnt_seq < 1 || cnt_seq > max_keep;
     const int cnt = cnt_seq < 0 ? 0 : (cnt_seq > max_keep ? max_keep : cnt_seq);
     const int r_begin = split * a.split_len;
+    if (split > 0 && r_begin >= cnt) return;  // the sequence ends before this split
     const int r_end = min(r_begin + a.split_len, cnt);
 
     RangeTab tab;
@@ -1505,7 +1548,7 @@ __global__ __launch_bounds__(256) void decode_attn_lds_kernel(const int32_t *__r
         nr.k = a.k_new + (int64_t)grp * kHeadDim;
         nr.v = a.v_new + (int64_t)grp * kHeadDim;
     }
-    uint8_t *st[2] = {&stages[wave][0][0], &stages[wave][kStages - 1][0]};
+    uint8_t *const stage = &stages[wave][0];
     uint8_t *ring[2] = {&idx_ring[kSrc != kSrcIndex ? 0 : wave][0][0], &idx_ring[kSrc != kSrcIndex ? 0 : wave][1][0]};
 
     WaveAcc w;
@@ -1519,87 +1562,63 @@ __global__ __launch_bounds__(256) void decode_attn_lds_kernel(const int32_t *__r
         materialize(tab.lo[1], tab.lo[2], tab.lo[3], tab.lo[4], tab.lo[5], tab.off[0], tab.off[1], tab.off[2],
                     tab.off[3], tab.off[4], tab.off[5]);
     const bool short_rows = a.s_pos < kRunRowLimit;
-    if (r < r_end && kStages == 1) {
-        int32_t pos[8];
-        if (kSrc == kSrcIndex) {
-            dma_idx(ring[0], irow, r, lane);
-            dma_idx(ring[1], irow, r + kSplitUnit, lane);
-        }
-        for (int k = 0;; r += kSplitUnit, ++k) {
-            if (kSrc != kSrcIndex) {
-                dma_pass_ranges<kRing, kAux>(st[0], tab, r, r_end, a.max_len, short_rows, kbase, vbase, a.s_pos, lane, c4,
-                                       w.bad_pos, nr);
-            } else {
-                wait_vm<1>();  // this pass's entries; the next pass's may stay in flight
-                dma_pos_index(ring[k & 1], r, r_end, a.max_len, c4, pos, w.bad_pos);
-                dma_pass<kAux>(st[0], kbase, vbase, a.s_pos, pos, lane, kRing, nr);
-            }
-            wait_vm<0>();
-            compute_pass_lds<true>(st[0], qf, min(kWaveTile, r_end - r), a.scale_log2, w, n16, c4);
-            if (r + kSplitUnit >= r_end) break;
-            if (kSrc == kSrcIndex) dma_idx(ring[k & 1], irow, r + 2 * kSplitUnit, lane);  // its slot is read
-        }
-    } else if (r < r_end) {
+    if (r < r_end) {
         int32_t pos[8];
         if (kSrc != kSrcIndex) {
-            dma_pass_ranges<kRing, kAux>(st[0], tab, r, r_end, a.max_len, short_rows, kbase, vbase, a.s_pos, lane, c4,
-                                   w.bad_pos, nr);
+            dma_pass_ranges<kRing, kAux>(stage, tab, r, r_end, a.max_len, short_rows, kbase, vbase, a.s_pos, lane, c4,
+                                         w.bad_pos, nr);
         } else {
             dma_idx(ring[0], irow, r, lane);
-            dma_idx(ring[1], irow, r + kSplitUnit, lane);
+            dma_idx(ring[1], irow, r + kUnit, lane);
             wait_vm<1>();
             dma_pos_index(ring[0], r, r_end, a.max_len, c4, pos, w.bad_pos);
-            dma_pass<kAux>(st[0], kbase, vbase, a.s_pos, pos, lane, kRing, nr);
+            dma_pass<kAux>(stage, kbase, vbase, a.s_pos, pos, lane, kRing, nr);
         }
-        for (int k = 0;; r += kSplitUnit, ++k) {
-            const uint8_t *cur = st[k & 1];
-            if (r + kSplitUnit < r_end) {
+        for (int k = 0;; r += kUnit, ++k) {
+            wait_vm<0>();  // this pass's rows (and the next pass's entries)
+            PassOperands ops;
+            read_operands(ops, stage, n16, c4);
+            const bool more = r + kUnit < r_end;
+            if (more) {  // the next pass's rows into the stage just read
                 if (kSrc != kSrcIndex) {
-                    dma_pass_ranges<kRing, kAux>(st[(k + 1) & 1], tab, r + kSplitUnit, r_end, a.max_len, short_rows, kbase,
-                                           vbase, a.s_pos, lane, c4, w.bad_pos, nr);
+                    dma_pass_ranges<kRing, kAux>(stage, tab, r + kUnit, r_end, a.max_len, short_rows, kbase, vbase,
+                                                 a.s_pos, lane, c4, w.bad_pos, nr);
                 } else {
-                    wait_vm<kStageLoads>();  // entries of the next pass (issued before this pass's rows)
-                    dma_pos_index(ring[(k + 1) & 1], r + kSplitUnit, r_end, a.max_len, c4, pos, w.bad_pos);
-                    dma_idx(ring[k & 1], irow, r + 2 * kSplitUnit, lane);
-                    dma_pass<kAux>(st[(k + 1) & 1], kbase, vbase, a.s_pos, pos, lane, kRing, nr);
+                    dma_pos_index(ring[(k + 1) & 1], r + kUnit, r_end, a.max_len, c4, pos, w.bad_pos);
+                    dma_idx(ring[k & 1], irow, r + 2 * kUnit, lane);  // its slot is read
+                    dma_pass<kAux>(stage, kbase, vbase, a.s_pos, pos, lane, kRing, nr);
                 }
-                if (kSrc != kSrcIndex)
-                    wait_vm<kStageLoads>();  // this pass's rows; the next pass's stay in flight
-                else
-                    wait_vm<kStageLoads + 1>();
-                compute_pass_lds<true>(cur, qf, kWaveTile, a.scale_log2, w, n16, c4);
-            } else {
-                wait_vm<0>();
-                compute_pass_lds<true>(cur, qf, min(kWaveTile, r_end - r), a.scale_log2, w, n16, c4);
-                break;
             }
+            compute_operands(ops, qf, min(kWaveTile, r_end - r), a.scale_log2, w, c4);
+            if (!more) break;
         }
     }
 
     if (kRing) store_new_row(a, app, nr, kbase, vbase, lane);
-    float *o_lds = reinterpret_cast<float *>(&stages[0][0][0]);  // each wavefront's O rows in its own stages
-    constexpr int kStageWaveFloats = kStages * kStageBytes / 4;
+    float *o_lds = reinterpret_cast<float *>(&stages[0][0]);  // each wavefront's O rows in its own stage
+    constexpr int kStageWaveFloats = kStageBytes / 4;
     publish_wave(w, o_lds + wave * kStageWaveFloats, cl, wave, n16, c4);
-    const int wg_bad_pos = barrier_or<kWavesPerWg>(w.bad_pos, s_wave_flag, wave, lane);
+    const int wg_bad_pos = barrier_or<kWaves>(w.bad_pos, s_wave_flag, wave, lane);
     const bool bad = wg_bad_pos || bad_count;
-    write_result(a, o_lds, kStageWaveFloats, cl, bad, G, tid, row0, a.n_split == 1,
-                 (uint32_t)grp * a.n_split + split);
+    // Splits the sequence has: those past its end have left, and take no part in
+    // the merge.
+    const int n = max(1, (cnt + a.split_len - 1) / a.split_len);
+    write_result(a, o_lds, kStageWaveFloats, cl, bad, G, tid, row0, n == 1, (uint32_t)grp * a.n_split + split);
     if ((kSrc == kSrcLayout || kRing) && g == 0 &&
         (layer == 0 || (pol_per_seq & MURMUR_POL_PER_LAYER)))  // per-layer policies: one set per layer
-        write_retained<kWavesPerWg * 64>(a, (pol_per_seq & MURMUR_POL_PER_LAYER) ? layer * B + b : b, cnt_seq,
+        write_retained<kWaves * 64>(a, (pol_per_seq & MURMUR_POL_PER_LAYER) ? layer * B + b : b, cnt_seq,
                                          policy_bad, rg,
-                       max_keep, tid, r_begin, r_begin + a.split_len);
+                       max_keep, tid, r_begin, split == n - 1 ? max_keep : r_begin + a.split_len);
     if (bad && tid == 0)
         raise_device_error((wg_bad_pos ? MURMUR_DEVERR_POSITION : 0) | (bad_count ? MURMUR_DEVERR_COUNT : 0));
-    if (a.n_split == 1) return;
-    constexpr int kThreads = kWavesPerWg * 64;
-    const int n = a.n_split;
-    const uint32_t pbase = (uint32_t)grp * n;
-    float *s_ml = reinterpret_cast<float *>(&stages[0][0][0]);
+    if (n == 1) return;
+    constexpr int kThreads = kWaves * 64;
+    const uint32_t pbase = (uint32_t)grp * a.n_split;
+    float *s_ml = reinterpret_cast<float *>(&stages[0][0]);
     const auto to_output = [&a, row0](int h, int d0, f32x4 O, float M, float L) {
         store_output(a, row0 + h, d0, O, M, L);
     };
-    if (n > 2 * kMergeBatch && n <= kTwoLevelMax) {
+    if (n > 2 * kMergeBatch && a.n_split <= kTwoLevelMax) {
         // Two levels: the last split of every kSubSplits folds their partials
         // into the first one's slot (one ticket per such set, after the group
         // tickets), and the last of those sets folds theirs into the output.
@@ -1612,7 +1631,8 @@ __global__ __launch_bounds__(256) void decode_attn_lds_kernel(const int32_t *__r
         const uint32_t sub0 = pbase + (uint32_t)(sub * kSubSplits);
         if (sub_n > 1) {
             const int groups = a.NL * a.B * a.Hkv;
-            if (!take_ticket(a, groups + grp * n_sub + sub, sub_n, tid, s_last)) return;
+            const int n_sub_all = (a.n_split + kSubSplits - 1) / kSubSplits;  // tickets laid out for every split
+            if (!take_ticket(a, groups + grp * n_sub_all + sub, sub_n, tid, s_last)) return;
             const __amdgpu_buffer_rsrc_t ro = raw_buffer(a.part_o, a.part_o_bytes);
             const __amdgpu_buffer_rsrc_t rml = raw_buffer(a.part_ml, a.part_ml_bytes);
             // Each thread reads the set's (h, d0) values and its head's pairs
@@ -1977,7 +1997,7 @@ __global__ __launch_bounds__(kWideThreads) void decode_attn_wide_kernel(
             dma_pass<kAux>(stage, kbase, vbase, a.s_pos, pos, lane, kRing, nr);
         }
         if (kSrc == kSrcLayout) layout_ok = layout_valid_late(lw);  // while this pass's rows are on their way
-        compute_pass_lds<false, true>(stage, qf, valid, a.scale_log2, w, n16, c4);
+        compute_pass_wide(stage, qf, valid, a.scale_log2, w, n16, c4);
     } else if (kSrc == kSrcLayout) {
         layout_ok = layout_valid_late(lw);
     }
@@ -2157,17 +2177,16 @@ static void launch_decode_attn_mode(const AttnLaunch &a, hipStream_t stream) {
                            a.q, a);
         return;
     }
-    const dim3 grid((unsigned)a.n_split, (unsigned)(a.NL * a.Hkv), (unsigned)a.B);
-    // Longer splits stage their passes in LDS, double-buffered within one
-    // dispatch round, else one stage per wavefront and two workgroups per
-    // compute unit.
+    const dim3 grid((unsigned)(a.NL * a.Hkv), (unsigned)a.B, (unsigned)a.n_split);
+    // Eight wavefronts and 128 KiB of LDS, a compute unit to itself, within one
+    // dispatch round; else four and 64 KiB, two workgroups per compute unit.
     const bool one_round = (int64_t)a.n_split * a.NL * a.Hkv * a.B <= kRoundWorkgroups;
     if (one_round)
-        hipLaunchKernelGGL((decode_attn_lds_kernel<kSrc, 2, kAux>), grid, dim3(kWavesPerWg * 64), 0, stream, a.src0,
-                           a.src1, a.idx, a.q, a.max_keep, a.B, a.pol_per_seq, a.Hkv, a.G, a);
+        hipLaunchKernelGGL((decode_attn_lds_kernel<kSrc, 8, kAux>), grid, dim3(8 * 64), 0, stream, a.src0, a.src1,
+                           a.idx, a.q, a.max_keep, a.B, a.pol_per_seq, a.Hkv, a.G, a);
     else
-        hipLaunchKernelGGL((decode_attn_lds_kernel<kSrc, 1, kAux>), grid, dim3(kWavesPerWg * 64), 0, stream, a.src0,
-                           a.src1, a.idx, a.q, a.max_keep, a.B, a.pol_per_seq, a.Hkv, a.G, a);
+        hipLaunchKernelGGL((decode_attn_lds_kernel<kSrc, 4, kAux>), grid, dim3(4 * 64), 0, stream, a.src0, a.src1,
+                           a.idx, a.q, a.max_keep, a.B, a.pol_per_seq, a.Hkv, a.G, a);
 }
 
 template <int kSrc>

@@ -1,0 +1,101 @@
+"""The LDS-staged kernel where its splits and passes end, against the oracle (MI355X).
+
+A sequence takes part with as many splits as its own count needs: the splits past its end leave without a
+partial, one split stores its output without a merge, and the merge (direct, in batches, two-level) is the one
+for that number.  Batches here mix sequences of one position up to all splits, with counts one short of, at and
+one past the ends of passes (32), of a pass of every wavefront (128 and 256) and of splits, on both workgroup
+sizes (grids within and beyond one dispatch round), through the range table, the index list, the fused step
+(retained-set outputs bit for bit) and ring storage, twice in a row (the tickets are back at zero).
+The tolerances are those of the parity tests (fp32 output, row-RMS-floored relative error)."""
+import numpy as np
+import pytest
+
+import oracle
+from _tol import LSE_TOL, REL_TOL, lse_err, rel_err_fp32
+from paper_2606_01483_amd import murmur as M
+from paper_2606_01483_amd import workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def ragged(counts, layers=1, hq=14, hkv=2, seed=77):
+    """Dense sequences that retain counts[b] positions at step 0: 3 prompt tokens, speech, and outputs."""
+    seg0 = []
+    for n in counts:
+        prompt = min(3, n - 1)
+        out = (n - prompt + 1) // 2
+        seg0.append([prompt, n - prompt - out, 0, out - 1])
+    return W.build("ragged", seed, layers, np.array(seg0, dtype=np.int32), np.array([W.OFF, 0, 0, W.OFF, 0]), 1,
+                   planted=False, hq=hq, hkv=hkv)
+
+
+def check(wl, db, run, what):
+    idx, cnt = oracle.retained(wl.seg(0), wl.policy)
+    ref, ref_lse = oracle.attend(wl.q(0), wl.k, wl.v, idx, cnt, scale=wl.scale)
+    for again in range(2):
+        print(f"[case] {what}, call {again}", flush=True)
+        db.out.fill_(float("nan"))
+        db.lse.fill_(float("nan"))
+        run()
+        torch.cuda.synchronize()
+        assert M.murmur_device_error() == 0
+        assert rel_err_fp32(db.out.cpu().numpy(), ref) <= REL_TOL, (what, again)
+        assert lse_err(db.lse.cpu().numpy(), ref_lse) <= LSE_TOL, (what, again)
+    return idx, cnt
+
+
+EDGES = [1, 31, 32, 33, 127, 128, 129, 255, 256, 257, 287, 288, 289, 511, 512, 513, 575, 576, 577, 1151, 1153]
+
+
+@pytest.mark.parametrize("split_len,layers", [(288, 1), (288, 4), (0, 1), (0, 8), (320, 2), (1024, 1)])
+def test_ragged_split_ends(split_len, layers):
+    from paper_2606_01483_amd.decode import DecodeBatch
+    counts = EDGES if split_len != 288 else EDGES + [288 * 8, 288 * 8 + 1, 288 * 16, 288 * 16 + 1, 288 * 18 - 5]
+    wl = ragged(counts, layers)
+    for use_ranges in (True, False):
+        db = DecodeBatch(wl, out_dtype=M.MURMUR_DTYPE_F32, steps=[0], split_len=split_len, use_ranges=use_ranges)
+        check(wl, db, lambda: db.step(0), f"split_len {split_len}, {layers} layers, ranges {use_ranges}")
+    for t in db.sets[0]:
+        t.fill_(-7)
+    idx, cnt = check(wl, db, lambda: db.step_fused(0), f"split_len {split_len}, {layers} layers, fused")
+    assert np.array_equal(db.count.cpu().numpy(), cnt)
+    assert np.array_equal(db.idx.cpu().numpy(), idx[:, :db.max_keep])
+
+
+@pytest.mark.parametrize("hq,hkv", [(4, 4), (16, 1)])
+def test_ragged_split_ends_group_sizes(hq, hkv):
+    from paper_2606_01483_amd.decode import DecodeBatch
+    wl = ragged(EDGES, 2, hq, hkv)
+    db = DecodeBatch(wl, out_dtype=M.MURMUR_DTYPE_F32, steps=[0], split_len=288)
+    check(wl, db, lambda: db.step(0), f"{hq} query heads, {hkv} KV heads")
+
+
+@pytest.mark.parametrize("split_len", [0, 96, 288])
+def test_ring_passes_around_the_current_row(split_len):
+    """Ring storage: passes that hold the current token's row (whose K/V come with the call) beside passes that
+    take consecutive rows, with rings of exactly the window and the current row at their start, middle and end."""
+    from paper_2606_01483_amd.decode import RingBatch
+    cap = 40
+    seg0 = np.array([[5, 300, 0, 40 + d] for d in (0, 1, 7, 31, 38, 39)], dtype=np.int32)
+    wl = W.build("ring", 78, 2, seg0, np.array([W.OFF, 0, 0, cap, 0]), 2, planted=False, hq=14, hkv=2)
+    rb = RingBatch(wl, cap, out_dtype=M.MURMUR_DTYPE_F32, steps=[0, 1], split_len=split_len)
+    for i in range(2):
+        print(f"[case] ring split_len {split_len} step {i}", flush=True)
+        rb.step(i)
+        torch.cuda.synchronize()
+        assert M.murmur_device_error() == 0
+        idx, cnt = oracle.retained(wl.seg(i), wl.policy)
+        ref, ref_lse = oracle.attend(wl.q(i), wl.k, wl.v, idx, cnt, scale=wl.scale)
+        assert rel_err_fp32(rb.out.cpu().numpy(), ref) <= REL_TOL
+        assert lse_err(rb.lse.cpu().numpy(), ref_lse) <= LSE_TOL
+
+
+@pytest.mark.parametrize("rows", [2047, 2048, 2049])
+def test_streamed_loads_on_both_sides_of_their_line(rows):
+    """Launches just under and over 8 MiB of K/V per layer (4096 positions of 4 KV heads), where the loads' cache
+    policy changes."""
+    from paper_2606_01483_amd.decode import DecodeBatch
+    wl = ragged([rows, rows], 1, 28, 4)
+    db = DecodeBatch(wl, out_dtype=M.MURMUR_DTYPE_F32, steps=[0])
+    check(wl, db, lambda: db.step_fused(0), f"2 x {rows} positions")
