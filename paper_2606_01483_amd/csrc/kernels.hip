@@ -364,8 +364,9 @@ static __device__ __forceinline__ float sum_over_c4(float x) {
 }
 
 // Running softmax state of one wavefront for one (layer, sequence, KV head):
-// lane (head n16, c4) holds the max (log2 units) and sum of head n16; acc[db][i]
-// is that head's O at head dim 16*db + 4*c4 + i.
+// lane (head n16, c4) holds the max (log2 units) of head n16 and the sum over the
+// ranks it holds itself (a quarter of them); acc[db][i] is that head's O at head
+// dim 16*db + 4*c4 + i.
 struct WaveAcc {
     float m_run, l_run;
     f32x4 acc[8];
@@ -454,43 +455,57 @@ static __device__ __forceinline__ void materialize(const T &...x) {
 // 16 + 4*c4 + 0..3), split into bf16 hi + lo so that hi + lo carries ~16
 // mantissa bits.  kOnline: fold into a running state; otherwise the state is
 // known to be empty.
+//
+// Bound by instruction issue (see decode_attn_lds_kernel), so what a pass does
+// not need is left out: the scale goes into the exponent's multiply-add where
+// no rank is masked; the sum stays per lane (over its own ranks) until the
+// state is published; and the running max, which only has to keep the
+// exponentials in range, stays where it is while no logit exceeds it by more
+// than kMaxSlack (then nothing is rescaled and no lane exchange is needed; the
+// weights are at most 2^kMaxSlack, and hi + lo carry them as before).
+constexpr float kMaxSlack = 4.f;
 template <bool kOnline>
 static __device__ __forceinline__ void softmax_step(const f32x4 (&s)[2], int valid, float scale_log2, WaveAcc &w,
                                                     int c4, u32x4 &p_hi, u32x4 &p_lo) {
-    // Logits in log2 units; ranks past `valid` are masked (a partial pass).
-    float x[2][4];
-    const bool partial = valid < kWaveTile;
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            x[blk][i] = s[blk][i] * scale_log2;
-            if (partial && 16 * blk + 4 * c4 + i >= valid) x[blk][i] = kNegInf;
-        }
-    float tmax = fmaxf(fmaxf(fmaxf(x[0][0], x[0][1]), fmaxf(x[0][2], x[0][3])),
-                       fmaxf(fmaxf(x[1][0], x[1][1]), fmaxf(x[1][2], x[1][3])));
-    tmax = max_over_c4(tmax);
-    const float m_new = kOnline ? fmaxf(w.m_run, tmax) : tmax;  // finite: rank 0 of the pass is valid
-    float pr[2][4];
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) pr[blk][i] = __builtin_amdgcn_exp2f(x[blk][i] - m_new);  // in [0, 1]
-    const float psum = sum_over_c4(((pr[0][0] + pr[0][1]) + (pr[0][2] + pr[0][3])) +
-                                   ((pr[1][0] + pr[1][1]) + (pr[1][2] + pr[1][3])));
-    if (kOnline) {
-        const float alpha = __builtin_amdgcn_exp2f(w.m_run - m_new);  // 0 while the state is empty
-        w.l_run = w.l_run * alpha + psum;
-        // A lane's O values belong to its own head.  Most passes raise no head's max
-        // (alpha is 1 in every lane).
-        if (__ballot(alpha != 1.f)) {
+    // Takes the max of this lane's logits (log2 units) into the state.
+    const auto raise_max = [&](float lane_max) {
+        if (!kOnline) {
+            w.m_run = max_over_c4(lane_max);
+        } else if (__ballot(lane_max > w.m_run + kMaxSlack)) {
+            const float m_new = fmaxf(w.m_run, max_over_c4(lane_max));
+            const float alpha = __builtin_amdgcn_exp2f(w.m_run - m_new);  // 0 while the state is empty
+            w.l_run *= alpha;
 #pragma unroll
             for (int db = 0; db < 8; ++db) w.acc[db] *= alpha;
+            w.m_run = m_new;
         }
+    };
+    float pr[2][4];
+    if (valid == kWaveTile && scale_log2 >= 0.f) {  // uniform
+        raise_max(fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])),
+                        fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3]))) *
+                  scale_log2);
+#pragma unroll
+        for (int blk = 0; blk < 2; ++blk)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                pr[blk][i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[blk][i], scale_log2, -w.m_run));
     } else {
-        w.l_run = psum;
+        float x[2][4];
+#pragma unroll
+        for (int blk = 0; blk < 2; ++blk)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                x[blk][i] = 16 * blk + 4 * c4 + i < valid ? s[blk][i] * scale_log2 : kNegInf;
+        raise_max(fmaxf(fmaxf(fmaxf(x[0][0], x[0][1]), fmaxf(x[0][2], x[0][3])),
+                        fmaxf(fmaxf(x[1][0], x[1][1]), fmaxf(x[1][2], x[1][3]))));
+#pragma unroll
+        for (int blk = 0; blk < 2; ++blk)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) pr[blk][i] = __builtin_amdgcn_exp2f(x[blk][i] - w.m_run);
     }
-    w.m_run = m_new;
+    const float psum = ((pr[0][0] + pr[0][1]) + (pr[0][2] + pr[0][3])) + ((pr[1][0] + pr[1][1]) + (pr[1][2] + pr[1][3]));
+    w.l_run = kOnline ? w.l_run + psum : psum;
 #pragma unroll
     for (int wd = 0; wd < 4; ++wd) {
         const int blk = wd >> 1, i0 = (wd & 1) * 2;
@@ -1135,9 +1150,10 @@ constexpr int kOWaveBytes = kMaxGroup * kOStride * 4;   // 8448: a wavefront's p
 template <int kWaves>
 static __device__ __forceinline__ void publish_wave(const WaveAcc &w, float *o_w, CombineLdsT<kWaves> &cl, int wave,
                                                     int n16, int c4) {
+    const float l = sum_over_c4(w.l_run);
     if (c4 == 0) {
         cl.ml[n16][wave][0] = w.m_run;
-        cl.ml[n16][wave][1] = w.l_run;
+        cl.ml[n16][wave][1] = l;
     }
 #pragma unroll
     for (int db = 0; db < 8; ++db)
