@@ -80,10 +80,30 @@ int64_t lds_auto_split(int64_t max_keep, int64_t groups) {
     return std::max<int64_t>(len, 2 * kSplitUnit);
 }
 
+// The split length of grids beyond one dispatch round, whose sequences may be
+// of very different lengths (0: one split each).  A sequence takes only the
+// splits it needs, so short ones stay whole and long ones are shared out; where
+// all are long, the cuts cost up to 1 % in partials and merges.  Measured (us,
+// whole -> 2048): 28 layers x 12 chunks, four layers dense, 129.6 -> 127.8; 14
+// layers x 24 chunks at all stages of their decode 377 -> 367; 28 layers x 12
+// chunks, all dense, 338 -> 342.  When all workgroups are resident at once (two
+// per compute unit) cutting adds a round: 28 layers x 4 chunks of 3400 120 ->
+// 133; only much longer sequences gain: 28 layers x 3 of 9000 to 27000 607 ->
+// 527.  At most kMaxAutoSplits splits, and 64 MiB of partials.
+int64_t long_split(int64_t max_keep, int64_t groups, int64_t G) {
+    if (groups <= kRoundWorkgroups) return 0;
+    if (max_keep < (groups > 2 * kRoundWorkgroups ? 3 * kLongSplit / 2 : 4 * kLongSplit)) return 0;
+    const int64_t least = ((max_keep + kMaxAutoSplits - 1) / kMaxAutoSplits + kWaveTile - 1) / kWaveTile * kWaveTile;
+    const int64_t len = std::max<int64_t>(kLongSplit, least);
+    const int64_t n = (max_keep + len - 1) / len;
+    const double bytes = (double)groups * (double)n * (double)G * (kHeadDim + 2) * 4.0;
+    return bytes <= (double)(64 << 20) ? len : 0;
+}
+
 }  // namespace
 
 WorkspacePlan plan_workspace(int32_t n_layers, int32_t B, int32_t Hq, int32_t Hkv, int32_t max_keep,
-                             int32_t split_len) {
+                             int32_t split_len, bool cut_long) {
     WorkspacePlan p{};
     const int64_t groups = (int64_t)n_layers * B * Hkv;
     const int64_t G = Hkv > 0 ? Hq / Hkv : 0;
@@ -135,7 +155,11 @@ WorkspacePlan plan_workspace(int32_t n_layers, int32_t B, int32_t Hq, int32_t Hk
             p.o_bytes = round_up((size_t)p.wide_wg * G * kHeadDim * sizeof(float), 256);
         }
     } else {
-        if (split_len <= 0) split_len = (int32_t)lds_auto_split(max_keep, groups);  // a whole compute unit each
+        if (split_len <= 0) {
+            split_len = (int32_t)lds_auto_split(max_keep, groups);  // a whole compute unit each
+            const int64_t cut = cut_long ? long_split(max_keep, groups, G) : 0;
+            if (cut > 0) split_len = (int32_t)cut;
+        }
         p.split_len = split_len;
         p.n_split = (int32_t)(((int64_t)max_keep + split_len - 1) / split_len);
         if (p.n_split > 1) {
@@ -237,7 +261,8 @@ int prepare_attn(const void *q_dev, const murmur_kv *kv, int32_t max_keep, int32
         return fail(MURMUR_EINVAL, "out_dev must be 16-byte and lse_dev 4-byte aligned");
     if (!aligned(ws_dev, 256)) return fail(MURMUR_EINVAL, "ws_dev must be 256-byte aligned");
 
-    const WorkspacePlan plan = plan_workspace(kv->n_layers, B, Hq, Hkv, max_keep, split_len);
+    WorkspacePlan plan = plan_workspace(kv->n_layers, B, Hq, Hkv, max_keep, split_len);
+    if (ws_bytes < plan.total) plan = plan_workspace(kv->n_layers, B, Hq, Hkv, max_keep, split_len, false);
     if (ws_bytes < plan.total && static_ws)
         return fail(MURMUR_ENOSPACE, "this call needs %zu bytes of scratch; the allocation-free step has %zu "
                     "(use murmur_decode_step with a workspace)", plan.total, ws_bytes);

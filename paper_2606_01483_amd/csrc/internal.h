@@ -14,6 +14,7 @@ constexpr int kMaxGroup = 16;     // query heads per KV head (MFMA tile height)
 constexpr int kWaveTile = 32;     // retained positions one wavefront handles per pass
 constexpr int kSplitUnit = 4 * kWaveTile;  // the LDS-staged schedule's split counts are chosen in units of 128 positions
 constexpr int kMaxAutoSplits = 64;
+constexpr int kLongSplit = 2048;          // see long_split (api.cpp)
 constexpr int kRoundWorkgroups = 256;     // one workgroup per compute unit
 // Splits one merge can combine: it stages 2 * n_split * G + 2 * G floats in
 // the workgroup's 32 KiB of V-tile LDS.
@@ -120,8 +121,11 @@ constexpr int kTicketStride = 32;
 size_t ticket_region(size_t ws_bytes);
 
 // Split choice and workspace layout; deterministic in its arguments.
+// cut_long: cut long sequences in grids of more than one dispatch round too
+// (without, such a launch needs no partials: for workspaces that cannot hold
+// them).
 WorkspacePlan plan_workspace(int32_t n_layers, int32_t B, int32_t Hq, int32_t Hkv, int32_t max_keep,
-                             int32_t split_len);
+                             int32_t split_len, bool cut_long = true);
 
 // Kernel launchers (kernels.hip).  They return a hipError_t value as int.
 int launch_evict_compact(const murmur_seg *seg, const murmur_policy *pol, int32_t pol_per_seq, int32_t B,
