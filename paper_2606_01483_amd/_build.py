@@ -2,7 +2,8 @@
 
 kernels.hip is compiled by hipcc for gfx950 only; api.cpp (host-only C ABI
 layer) by g++.  The shared object lands next to this file, where the ctypes
-binding loads it.  Packed-fp32 instruction selection is disabled for device
+binding loads it, and beside it _pycall.so, the argument converter of the
+per-step calls (pycall.cpp).  Packed-fp32 instruction selection is disabled for device
 code, and the first 16 kernel-argument dwords are preloaded into SGPRs.  Only
 the murmur_* entry points are exported.
 """
@@ -11,12 +12,14 @@ from __future__ import annotations
 import os
 import shutil
 import subprocess
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libmurmur.so")
+PYCALL = os.path.join(PKG, "_pycall.so")
 BUILD_DIR = os.path.join(ROOT, "_build")
 ARCH = "gfx950"
 
@@ -60,6 +63,13 @@ def build(verbose: bool = False) -> str:
         print(" ".join(link), flush=True)
     _run(link)
     os.replace(tmp, LIB)
+    tmp = PYCALL + ".tmp"
+    cmd = ["g++", *COMMON_FLAGS, "-Wextra", "-shared", f"-I{sysconfig.get_paths()['include']}",
+           os.path.join(CSRC, "pycall.cpp"), "-o", tmp]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    _run(cmd)
+    os.replace(tmp, PYCALL)
     return LIB
 
 

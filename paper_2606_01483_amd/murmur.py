@@ -57,6 +57,15 @@ class MurmurError(RuntimeError):
 
 _lib = None
 
+# The per-step entry points convert their arguments in C (csrc/pycall.cpp) where that module is built; an argument
+# it does not take, or a build without it, goes through ctypes.  Both call the same library.
+_PER_STEP = ("evict_compact", "evict_compact_paged", "decode_attn", "decode_step", "decode_step_static",
+             "decode_step_ring", "paged_step")
+try:
+    from . import _pycall
+except ImportError:
+    _pycall = None
+
 
 def _load():
     global _lib
@@ -114,6 +123,9 @@ def _load():
     lib.murmur_read_probe.argtypes = [vp, sz, i32, i32, i32, i32, vp, vp]
     lib.murmur_device_error.restype = ctypes.c_int
     lib.murmur_device_error.argtypes = [vp, i32p]
+    # (C function, its address, the converter) of each per-step entry point
+    lib.per_step = {n: (getattr(lib, "murmur_" + n), ctypes.cast(getattr(lib, "murmur_" + n), vp).value,
+                        getattr(_pycall, n, None)) for n in _PER_STEP}
     _lib = lib
     return lib
 
@@ -137,13 +149,43 @@ def _addr(x) -> int | None:
     return x.data_ptr()
 
 
+_raw_stream = None
+
+
+def _current_stream() -> int:
+    """The current torch stream's handle, without building a torch.cuda.Stream where torch offers it."""
+    global _raw_stream
+    if _raw_stream is None:
+        import torch
+        handle = torch.cuda.current_stream().cuda_stream  # initialises CUDA
+        raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+        if raw is not None and device is not None:
+            _raw_stream = lambda: raw(device())  # noqa: E731
+        else:
+            _raw_stream = lambda: torch.cuda.current_stream().cuda_stream  # noqa: E731
+        return handle
+    return _raw_stream()
+
+
 def _stream(stream) -> int | None:
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
+
+
+def _call(name: str, *args) -> None:
+    """Calls murmur_<name>; device buffers are tensors, addresses or None, structures ctypes structures."""
+    fn, address, convert = _load().per_step[name]
+    if convert is not None:
+        rc = convert(address, *args)
+        if rc is not NotImplemented:
+            if rc != MURMUR_OK:
+                _check(rc)
+            return
+    _check(fn(*[ctypes.byref(x) if isinstance(x, ctypes.Structure) else _addr(x) if t is ctypes.c_void_p else x
+                for x, t in zip(args, fn.argtypes)]))
 
 
 def _segs(seg) -> ctypes.Array:
@@ -189,17 +231,16 @@ def murmur_evict_compact(seg_dev, pol_dev, pol_per_seq: int, B: int, idx_dev, ma
                          ranges_dev=None, stream=None) -> None:
     """seg_dev: int32 [B,4] device tensor; pol_dev: int32 [1 or B, 5]; idx_dev: int32 [B, max_keep];
     count_dev: int32 [B]; ranges_dev: int32 [B, 6, 2] or None."""
-    _check(_load().murmur_evict_compact(_addr(seg_dev), _addr(pol_dev), pol_per_seq, B, _addr(idx_dev), max_keep,
-                                        _addr(count_dev), _addr(ranges_dev), _stream(stream)))
+    _call("evict_compact", seg_dev, pol_dev, pol_per_seq, B, idx_dev, max_keep, count_dev, ranges_dev,
+          _stream(stream))
 
 
 def murmur_evict_compact_paged(seg_dev, pol_dev, pol_per_seq: int, B: int, block_table_dev, max_blocks: int,
                                block_size: int, idx_dev, max_keep: int, count_dev, ranges_dev=None,
                                stream=None) -> None:
     """murmur_evict_compact with the index list in rows of a paged pool (block_table_dev int32 [B, max_blocks])."""
-    _check(_load().murmur_evict_compact_paged(_addr(seg_dev), _addr(pol_dev), pol_per_seq, B, _addr(block_table_dev),
-                                              max_blocks, block_size, _addr(idx_dev), max_keep, _addr(count_dev),
-                                              _addr(ranges_dev), _stream(stream)))
+    _call("evict_compact_paged", seg_dev, pol_dev, pol_per_seq, B, block_table_dev, max_blocks, block_size, idx_dev,
+          max_keep, count_dev, ranges_dev, _stream(stream))
 
 
 def murmur_decode_attn_workspace(n_layers: int, B: int, Hq: int, Hkv: int, max_keep: int, split_len: int = 0) -> int:
@@ -227,30 +268,24 @@ def kv_from_tensors(k, v) -> murmur_kv:
 def murmur_decode_attn(q_dev, kv: murmur_kv, idx_dev, ranges_dev, count_dev, max_keep: int, B: int, Hq: int,
                        Hkv: int, D: int, scale: float, split_len: int, out_dev, out_dtype: int, lse_dev, ws_dev,
                        ws_bytes: int, stream=None) -> None:
-    _check(_load().murmur_decode_attn(_addr(q_dev), ctypes.byref(kv), _addr(idx_dev), _addr(ranges_dev),
-                                      _addr(count_dev), max_keep, B, Hq, Hkv, D, float(scale), split_len,
-                                      _addr(out_dev), out_dtype, _addr(lse_dev), _addr(ws_dev), ws_bytes,
-                                      _stream(stream)))
+    _call("decode_attn", q_dev, kv, idx_dev, ranges_dev, count_dev, max_keep, B, Hq, Hkv, D, float(scale), split_len,
+          out_dev, out_dtype, lse_dev, ws_dev, ws_bytes, _stream(stream))
 
 
 def murmur_decode_step(seg_dev, pol_dev, pol_per_seq: int, q_dev, kv: murmur_kv, idx_dev, count_dev, ranges_dev,
                        max_keep: int, B: int, Hq: int, Hkv: int, D: int, scale: float, split_len: int, out_dev,
                        out_dtype: int, lse_dev, ws_dev, ws_bytes: int, stream=None) -> None:
     """Eviction and attention of one decode step in one launch; idx/count/ranges outputs are optional."""
-    _check(_load().murmur_decode_step(_addr(seg_dev), _addr(pol_dev), pol_per_seq, _addr(q_dev), ctypes.byref(kv),
-                                      _addr(idx_dev), _addr(count_dev), _addr(ranges_dev), max_keep, B, Hq, Hkv, D,
-                                      float(scale), split_len, _addr(out_dev), out_dtype, _addr(lse_dev),
-                                      _addr(ws_dev), ws_bytes, _stream(stream)))
+    _call("decode_step", seg_dev, pol_dev, pol_per_seq, q_dev, kv, idx_dev, count_dev, ranges_dev, max_keep, B, Hq, Hkv,
+          D, float(scale), split_len, out_dev, out_dtype, lse_dev, ws_dev, ws_bytes, _stream(stream))
 
 
 def murmur_decode_step_static(seg_dev, pol_dev, pol_per_seq: int, q_dev, kv: murmur_kv, idx_dev, count_dev,
                               ranges_dev, max_keep: int, B: int, Hq: int, Hkv: int, D: int, scale: float,
                               split_len: int, out_dev, out_dtype: int, lse_dev, stream=None) -> None:
     """murmur_decode_step without a workspace: tickets and partials in the library's per-device scratch."""
-    _check(_load().murmur_decode_step_static(_addr(seg_dev), _addr(pol_dev), pol_per_seq, _addr(q_dev),
-                                             ctypes.byref(kv), _addr(idx_dev), _addr(count_dev), _addr(ranges_dev),
-                                             max_keep, B, Hq, Hkv, D, float(scale), split_len, _addr(out_dev),
-                                             out_dtype, _addr(lse_dev), _stream(stream)))
+    _call("decode_step_static", seg_dev, pol_dev, pol_per_seq, q_dev, kv, idx_dev, count_dev, ranges_dev, max_keep, B,
+          Hq, Hkv, D, float(scale), split_len, out_dev, out_dtype, lse_dev, _stream(stream))
 
 
 MURMUR_STATIC_SCRATCH_BYTES = 4 << 20
@@ -290,10 +325,8 @@ def murmur_paged_step(seg_dev, pol_dev, pol_per_seq: int, B: int, block_table_de
                       pool: murmur_kv | None = None, Hkv: int = 0, k_new_dev=None, v_new_dev=None,
                       stream=None) -> None:
     """Device block manager of a paged cache for one decode step (free, allocate, append the current K/V)."""
-    _check(_load().murmur_paged_step(_addr(seg_dev), _addr(pol_dev), pol_per_seq, B, _addr(block_table_dev),
-                                     max_blocks, block_size, _addr(free_stack_dev), _addr(free_top_dev), capacity,
-                                     int(bool(full_scan)), ctypes.byref(pool) if pool is not None else None, Hkv,
-                                     _addr(k_new_dev), _addr(v_new_dev), _stream(stream)))
+    _call("paged_step", seg_dev, pol_dev, pol_per_seq, B, block_table_dev, max_blocks, block_size, free_stack_dev,
+          free_top_dev, capacity, int(bool(full_scan)), pool, Hkv, k_new_dev, v_new_dev, _stream(stream))
 
 
 def make_ring(out_capacity: int, k_new, v_new) -> murmur_ring:
@@ -306,11 +339,8 @@ def murmur_decode_step_ring(seg_dev, pol_dev, pol_per_seq: int, ring: murmur_rin
                             split_len: int, out_dev, out_dtype: int, lse_dev, ws_dev, ws_bytes: int,
                             stream=None) -> None:
     """Eviction, attention and the current token's append on ring storage, in one launch."""
-    _check(_load().murmur_decode_step_ring(_addr(seg_dev), _addr(pol_dev), pol_per_seq, ctypes.byref(ring),
-                                           _addr(q_dev), ctypes.byref(kv), _addr(idx_dev), _addr(count_dev),
-                                           _addr(ranges_dev), max_keep, B, Hq, Hkv, D, float(scale), split_len,
-                                           _addr(out_dev), out_dtype, _addr(lse_dev), _addr(ws_dev), ws_bytes,
-                                           _stream(stream)))
+    _call("decode_step_ring", seg_dev, pol_dev, pol_per_seq, ring, q_dev, kv, idx_dev, count_dev, ranges_dev, max_keep,
+          B, Hq, Hkv, D, float(scale), split_len, out_dev, out_dtype, lse_dev, ws_dev, ws_bytes, _stream(stream))
 
 
 def murmur_plan_chunks(seg_start, seg_end, audio_len: float, max_chunk: float = 300.0,
