@@ -462,8 +462,13 @@ static __device__ __forceinline__ void materialize(const T &...x) {
 // state is published; and the running max, which only has to keep the
 // exponentials in range, stays where it is while no logit exceeds it by more
 // than kMaxSlack (then nothing is rescaled and no lane exchange is needed; the
-// weights are at most 2^kMaxSlack, and hi + lo carry them as before).
+// weights are at most 2^kMaxSlack, and hi + lo carry them as before).  The max
+// is a rounded product and the multiply-add subtracts it from the exact one, at
+// most half a unit in the last place above it: nothing below kMaxFused, but of
+// a max of 2^31 or more it would overflow the exponential, so logits near such
+// a max are rounded before the subtraction.
 constexpr float kMaxSlack = 4.f;
+constexpr float kMaxFused = 0x1p26f;
 template <bool kOnline>
 static __device__ __forceinline__ void softmax_step(const f32x4 (&s)[2], int valid, float scale_log2, WaveAcc &w,
                                                     int c4, u32x4 &p_hi, u32x4 &p_lo) {
@@ -481,10 +486,14 @@ static __device__ __forceinline__ void softmax_step(const f32x4 (&s)[2], int val
         }
     };
     float pr[2][4];
-    if (valid == kWaveTile && scale_log2 >= 0.f) {  // uniform
+    bool fused = valid == kWaveTile && scale_log2 >= 0.f;  // uniform
+    if (fused) {
         raise_max(fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])),
                         fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3]))) *
                   scale_log2);
+        fused = !__ballot(fabsf(w.m_run) > kMaxFused);
+    }
+    if (fused) {
 #pragma unroll
         for (int blk = 0; blk < 2; ++blk)
 #pragma unroll

@@ -99,3 +99,15 @@ def test_streamed_loads_on_both_sides_of_their_line(rows):
     wl = ragged([rows, rows], 1, 28, 4)
     db = DecodeBatch(wl, out_dtype=M.MURMUR_DTYPE_F32, steps=[0])
     check(wl, db, lambda: db.step_fused(0), f"2 x {rows} positions")
+
+
+@pytest.mark.parametrize("scale", [1e6, -1e6, 1e12, -1e12, 1e30])
+@pytest.mark.parametrize("split_len,layers", [(96, 1), (288, 1), (288, 8)])
+def test_logits_far_apart(split_len, layers, scale):
+    """Logits whose spacing in fp32 is far above one: the weights are one-hot and every exponent stays in range.
+    lse is the largest logit then, so the tolerances of ordinary logits hold."""
+    from paper_2606_01483_amd.decode import DecodeBatch
+    wl = ragged([64, 300, 577, 700], layers)
+    wl.scale = scale
+    db = DecodeBatch(wl, out_dtype=M.MURMUR_DTYPE_F32, steps=[0], split_len=split_len)
+    check(wl, db, lambda: db.step_fused(0), f"scale {scale}, split_len {split_len}, {layers} layers")
