@@ -689,11 +689,13 @@ static __device__ __forceinline__ void dma_pass_run(uint8_t *stage, const uint16
 }
 
 // The 16 K/V loads of the pass at ranks r0 .. min(r0 + kWaveTile, r_end) - 1
-// from the range table: consecutive rows through dma_pass_run (tab_run; in
-// ring storage, passes that hold the current row, which comes from another
-// buffer, are left out: one pass in a sequence's retained set, where taking
-// them all per row cost 0.3 us on 12 x 300 s), else per-row positions through
-// dma_pass.  short_rows: stride_pos < kRunRowLimit.
+// from the range table: consecutive rows through dma_pass_run (tab_run), else
+// per-row positions through dma_pass.  short_rows: stride_pos < kRunRowLimit.
+// In ring storage the current row comes from another buffer, so the one pass
+// that holds it goes per row; and a small launch (normal cache policy) sends all
+// passes per row, since its few passes mostly cross pieces and the test and the
+// second path only cost: 162 rows 5.70 us with it and 5.44 without, 5 x 230 rows
+// 6.25 and 6.16, but 12 x 850 rows (streamed) 8.5 and 8.8.
 template <bool kRing, int kAux>
 static __device__ __forceinline__ void dma_pass_ranges(uint8_t *stage, const RangeTab &tab, int r0, int r_end,
                                                        int max_len, bool short_rows, const uint16_t *kbase,
@@ -701,7 +703,7 @@ static __device__ __forceinline__ void dma_pass_ranges(uint8_t *stage, const Ran
                                                        int &bad, const NewRows &nr) {
     const int valid = min(kWaveTile, r_end - r0);
     int p0;
-    if (short_rows && tab_run(tab, r0, valid, max_len, p0) &&
+    if ((!kRing || kAux == kAuxStream) && short_rows && tab_run(tab, r0, valid, max_len, p0) &&
         (!kRing || (uint32_t)(nr.cur - p0) >= (uint32_t)valid)) {
         if (valid == kWaveTile)
             dma_pass_run<true, kAux>(stage, kbase, vbase, s_pos, p0, valid, lane);
