@@ -2180,14 +2180,13 @@ static bool small_group_offsets(const AttnLaunch &a) {
 
 // Whether a launch streams its K/V rows past the L2s (see kAuxStream): when a
 // layer's retained rows come to at least kStreamBytes.  Below that, the rows of
-// all layers of a 28-layer decoder (235 MB) fit the 256 MB Infinity Cache, and
-// small ones the 32 MB of L2, so the next token may find them there, and then
-// the normal policy is the faster one.  One cache of 28 layers read again and
-// again, us per launch, normal / streamed: 0.4 MB a layer 4.56 / 5.21, 3.5 MB
-// 5.92 / 6.20, 5.3 MB 6.70 / 7.35, 7.0 MB 6.30 / 6.31, 10.4 MB 6.82 / 6.79,
-// 14 MB 7.33 / 7.18; three caches read in turn, so that less survives: 1.7 MB
-// 5.90 / 6.12, 3.5 MB 6.23 / 6.12, 8.7 MB 6.97 / 6.63, 14 MB 7.65 / 7.21.
-constexpr double kStreamBytes = 8 << 20;
+// all layers of a decoder may fit the 256 MB Infinity Cache, and small ones the
+// 32 MB of L2, so the next token may find them there, and then the normal
+// policy is the faster one.  One cache of 28 layers read again and again, us
+// per launch, normal / streamed: 0.4 MB a layer 4.56 / 5.21, 3.5 MB 5.92 /
+// 6.20, 7.0 MB 6.30 / 6.31, 11.4 MB 8.27 / 8.03, 14 MB 7.44 / 7.11; of 3 or 4
+// layers: 11.4 MB 8.12 / 8.86, 14 MB 7.92 / 7.90.
+constexpr double kStreamBytes = 12 << 20;
 static bool stream_rows(const AttnLaunch &a) {
     return (double)a.B * a.Hkv * a.max_keep * (2 * kHeadDim * 2) >= kStreamBytes;
 }

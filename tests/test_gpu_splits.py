@@ -93,12 +93,12 @@ def test_ring_passes_around_the_current_row(split_len):
 
 @pytest.mark.parametrize("rows", [2047, 2048, 2049])
 def test_streamed_loads_on_both_sides_of_their_line(rows):
-    """Launches just under and over 8 MiB of K/V per layer (4096 positions of 4 KV heads), where the loads' cache
+    """Launches just under and over 12 MiB of K/V per layer (6144 positions of 4 KV heads), where the loads' cache
     policy changes."""
     from paper_2606_01483_amd.decode import DecodeBatch
-    wl = ragged([rows, rows], 1, 28, 4)
+    wl = ragged([rows, rows, rows], 1, 28, 4)
     db = DecodeBatch(wl, out_dtype=M.MURMUR_DTYPE_F32, steps=[0])
-    check(wl, db, lambda: db.step_fused(0), f"2 x {rows} positions")
+    check(wl, db, lambda: db.step_fused(0), f"3 x {rows} positions")
 
 
 @pytest.mark.parametrize("scale", [1e6, -1e6, 1e12, -1e12, 1e30])
