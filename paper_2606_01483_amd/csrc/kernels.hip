@@ -457,62 +457,79 @@ static __device__ __forceinline__ void materialize(const T &...x) {
 // known to be empty.
 //
 // Bound by instruction issue (see decode_attn_lds_kernel), so what a pass does
-// not need is left out: the scale goes into the exponent's multiply-add where
-// no rank is masked; the sum stays per lane (over its own ranks) until the
-// state is published; and while no head's max rises nothing is rescaled and no
-// lane exchange is needed.  The running max follows every rise: letting it lag
-// by up to 4 saved 0.6 % on 12 x 300 s dense and 1.4 % on 16 chunks from range
-// tables, but then the largest weight is no longer exactly one and takes the
-// rounding of hi + lo too (28 layers with planted keys: 1.9e-6 off, not 1.3e-6).
+// not need is left out: the scale goes into the exponent's multiply-add; the sum
+// stays per lane (over its own ranks) until the state is published; and while no
+// head's max rises nothing is rescaled and no lane exchange is needed.  The
+// running max follows every rise: letting it lag by up to 4 saved 0.6 % on 12 x
+// 300 s dense and 1.4 % on 16 chunks from range tables, but then the largest
+// weight takes the rounding of hi + lo too (28 layers with planted keys: 1.9e-6
+// off, not 1.3e-6).
 //
 // The max is a rounded product and the multiply-add subtracts it from the exact
-// one, at most half a unit in the last place above it: nothing below kMaxFused,
-// but of a max of 2^31 or more it would overflow the exponential, so logits near
-// such a max are rounded before the subtraction.
-constexpr float kMaxFused = 0x1p26f;
+// one, so the largest weight is not exactly one but 2^d, |d| at most half a unit
+// in the last place of the max: 2^-9 below kMaxFused, where its distance from one
+// still lies in the lo part.  Far above, it would lose lo's bits (at 2^26 |d| is
+// 2) and from 2^31 overflow or vanish, so a head with such a max subtracts
+// rounded products, whose error is of the same order.  Which of the two a weight
+// takes depends on the running max of its own head alone, not on whether its pass
+// is whole or on the other heads: equal logits weigh the same in every pass.
+constexpr float kMaxFused = 0x1p16f;
 template <bool kOnline>
-static __device__ __forceinline__ void softmax_step(const f32x4 (&s)[2], int valid, float scale_log2, WaveAcc &w,
+static __device__ __forceinline__ void softmax_step(const f32x4 (&s_all)[2], int valid, float scale_log2, WaveAcc &w,
                                                     int c4, u32x4 &p_hi, u32x4 &p_lo) {
-    // Takes the max of this lane's logits (log2 units) into the state.
-    const auto raise_max = [&](float lane_max) {
-        if (!kOnline) {
-            w.m_run = max_over_c4(lane_max);
-        } else if (__ballot(lane_max > w.m_run)) {
-            const float m_new = fmaxf(w.m_run, max_over_c4(lane_max));
-            const float alpha = __builtin_amdgcn_exp2f(w.m_run - m_new);  // 0 while the state is empty
-            w.l_run *= alpha;
+    // One path for whole and partial passes, and everything else out of its way:
+    // a launch of one pass pays for each line of code it fetches (a second copy
+    // for partial passes cost 0.05 us of 4.5).
+    f32x4 s[2] = {s_all[0], s_all[1]};
+    const auto in_pass = [valid, c4](int blk, int i) { return 16 * blk + 4 * c4 + i < valid; };
+    if (valid < kWaveTile) {
 #pragma unroll
-            for (int db = 0; db < 8; ++db) w.acc[db] *= alpha;
-            w.m_run = m_new;
-        }
-    };
-    float pr[2][4];
-    bool fused = valid == kWaveTile && scale_log2 >= 0.f;  // uniform
-    if (fused) {
-        raise_max(fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])),
-                        fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3]))) *
-                  scale_log2);
-        fused = !__ballot(fabsf(w.m_run) > kMaxFused);
+        for (int blk = 0; blk < 2; ++blk)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s[blk][i] = in_pass(blk, i) ? s[blk][i] : kNegInf;
     }
-    if (fused) {
+    const bool positive = scale_log2 > 0.f;  // uniform; a masked logit is -inf then
+    float lane_max;                          // of this lane's logits, log2 units
+    if (__builtin_expect(positive, 1)) {
+        lane_max = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])),
+                         fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3]))) *
+                   scale_log2;
+    } else {
+        lane_max = kNegInf;
+#pragma unroll
+        for (int blk = 0; blk < 2; ++blk)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                lane_max = fmaxf(lane_max, in_pass(blk, i) ? s[blk][i] * scale_log2 : kNegInf);
+    }
+    if (!kOnline) {
+        w.m_run = max_over_c4(lane_max);
+    } else if (__ballot(lane_max > w.m_run)) {
+        const float m_new = fmaxf(w.m_run, max_over_c4(lane_max));
+        const float alpha = __builtin_amdgcn_exp2f(w.m_run - m_new);  // 0 while the state is empty
+        w.l_run *= alpha;
+#pragma unroll
+        for (int db = 0; db < 8; ++db) w.acc[db] *= alpha;
+        w.m_run = m_new;
+    }
+    float pr[2][4];
+    const bool far = fabsf(w.m_run) > kMaxFused;
+    if (__builtin_expect(positive && !__ballot(far), 1)) {
 #pragma unroll
         for (int blk = 0; blk < 2; ++blk)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 pr[blk][i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[blk][i], scale_log2, -w.m_run));
     } else {
-        float x[2][4];
 #pragma unroll
         for (int blk = 0; blk < 2; ++blk)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                x[blk][i] = 16 * blk + 4 * c4 + i < valid ? s[blk][i] * scale_log2 : kNegInf;
-        raise_max(fmaxf(fmaxf(fmaxf(x[0][0], x[0][1]), fmaxf(x[0][2], x[0][3])),
-                        fmaxf(fmaxf(x[1][0], x[1][1]), fmaxf(x[1][2], x[1][3]))));
-#pragma unroll
-        for (int blk = 0; blk < 2; ++blk)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) pr[blk][i] = __builtin_amdgcn_exp2f(x[blk][i] - w.m_run);
+            for (int i = 0; i < 4; ++i) {
+#pragma clang fp contract(off)
+                const float x = s[blk][i] * scale_log2;
+                const float e = far ? x - w.m_run : __builtin_fmaf(s[blk][i], scale_log2, -w.m_run);
+                pr[blk][i] = __builtin_amdgcn_exp2f(in_pass(blk, i) ? e : kNegInf);
+            }
     }
     const float psum = ((pr[0][0] + pr[0][1]) + (pr[0][2] + pr[0][3])) + ((pr[1][0] + pr[1][1]) + (pr[1][2] + pr[1][3]));
     w.l_run = kOnline ? w.l_run + psum : psum;

@@ -111,3 +111,43 @@ def test_logits_far_apart(split_len, layers, scale):
     wl.scale = scale
     db = DecodeBatch(wl, out_dtype=M.MURMUR_DTYPE_F32, steps=[0], split_len=split_len)
     check(wl, db, lambda: db.step_fused(0), f"scale {scale}, split_len {split_len}, {layers} layers")
+
+
+def equal_logits(counts, layers):
+    """Heads whose logits are the same at every position, of magnitudes 2^9 to 2^26 in log2 units, and one whose
+    logits rise across 2^16 with the rank (their top value at the last positions of a sequence, over more than
+    one pass of 32 wherever there is one)."""
+    wl = ragged(counts, layers)
+    k = np.zeros(wl.k.shape, dtype=np.float32)
+    k[..., 0] = 1.3046875
+    for b, n in enumerate(counts):
+        k[:, b, :, :n, 1] = 2.0 ** np.minimum(np.arange(n) * 4 // max(1, n - 40), 3)
+    past = wl.k == W.BF16_NAN
+    wl.k = np.where(past, wl.k, W.f32_to_bf16_bits(k))
+    q = np.zeros((layers, wl.batch, wl.hq, 128), dtype=np.float32)
+    group = wl.hq // wl.hkv
+    x = np.array([0.7 * 2**9, 1.3 * 2**14, 1.6 * 2**23, 1.7 * 2**24, -1.3 * 2**14, 0, 1])[:group]
+    q[..., 0] = np.tile(x, wl.hkv)
+    q[..., group - 2::group, 1] = 0.7 * 2**14  # x is 0 for this head
+    bits = W.f32_to_bf16_bits(q)
+    wl.q = lambda step: bits
+    return wl
+
+
+@pytest.mark.parametrize("scale", [1.0, -1.0, 0.0])
+@pytest.mark.parametrize("split_len,layers", [(96, 1), (288, 1), (288, 8), (1024, 1)])
+def test_equal_logits_weigh_the_same_in_every_pass(split_len, layers, scale):
+    """A position's weight does not depend on the pass that holds it, whole or a sequence's last partial one, nor
+    on the other heads of its group: with equal logits the output is the mean of V.  Bound: the weights carry 17
+    bits (bf16 hi + lo) and cancel against their own sum, 2^-17 in relative terms, times four."""
+    from paper_2606_01483_amd.decode import DecodeBatch
+    counts = [33, 40, 47, 63, 95, 129, 300, 577, 1100]
+    wl = equal_logits(counts, layers)
+    wl.scale = scale
+    for use_ranges in (True, False):
+        db = DecodeBatch(wl, out_dtype=M.MURMUR_DTYPE_F32, steps=[0], split_len=split_len, use_ranges=use_ranges)
+        idx, cnt = check(wl, db, lambda: db.step(0), f"equal logits, split_len {split_len}, scale {scale}")
+        assert cnt.tolist() == counts
+        ref, _ = oracle.attend(wl.q(0), wl.k, wl.v, idx, cnt, scale=wl.scale)
+        err = rel_err_fp32(db.out.cpu().numpy(), ref)
+        assert err <= 4 * 2.0**-17
