@@ -265,8 +265,16 @@ int murmur_paged_step(const murmur_seg *seg_dev, const murmur_policy *pol_dev, i
  * and the split partials after that region.  It must be zero-filled once
  * before its first use (or reset with murmur_decode_attn_workspace_init);
  * every completed call leaves the tickets at zero again.  Calls of any shapes
- * may share a workspace as long as they pass the same ws_bytes (at least what
- * this function returns for each of them) and do not run concurrently. */
+ * may share a workspace as long as they pass the same ws_bytes (enough for each
+ * of them) and do not run concurrently.
+ * With split_len 0 and more than 256 groups a call needs 256 bytes, and the
+ * returned size may hold more: the partials (at most 64 MiB, with the tickets at
+ * most 74) of a cut of long groups into splits of 2048 positions or more, which
+ * the call then makes from max_keep 8192 on in up to 320 groups, from 10240 in up
+ * to 352, and with policies per layer (MURMUR_POL_PER_LAYER) from 8192 in up to
+ * 512 groups and from 3072 in more.  A call with less workspace keeps its groups
+ * whole; its result is the same up to the rounding of the fp32 sums.  In every
+ * other case the returned size is required. */
 int murmur_decode_attn_workspace(int32_t n_layers, int32_t B, int32_t Hq, int32_t Hkv, int32_t max_keep,
                                  int32_t split_len, size_t *bytes);
 
@@ -297,12 +305,15 @@ int murmur_decode_attn_workspace_init(void *ws_dev, size_t ws_bytes, murmur_stre
  *               passes of 32 positions in turn), merged by log-sum-exp.
  *               0: automatic split length (at most one dispatch round of
  *               workgroups when the work is small, at most 64 splits per
- *               group otherwise);
+ *               group otherwise; for more than 256 groups it depends on
+ *               whether the workspace holds the partials, see
+ *               murmur_decode_attn_workspace);
  *   out_dev:    [n_layers][B][Hq][D] of out_dtype, 16-byte aligned
  *               (MURMUR_DTYPE_BF16 rounds to nearest even, MURMUR_DTYPE_F32
  *               stores the fp32 accumulation);
  *   lse_dev:    nullable fp32 [n_layers][B][Hq], natural log;
- *   ws_dev:     workspace of ws_bytes >= murmur_decode_attn_workspace(...).
+ *   ws_dev:     workspace of ws_bytes >= murmur_decode_attn_workspace(...), or
+ *               at least 256 bytes where that function says so.
  * Accumulation is fp32 throughout.  Errors: MURMUR_EINVAL, MURMUR_EUNSUPPORTED
  * (head_dim, group size, max_keep above 2^28), MURMUR_ENOSPACE (workspace),
  * MURMUR_EHIP; device errors
@@ -349,9 +360,9 @@ int murmur_decode_step(const murmur_seg *seg_dev, const murmur_policy *pol_dev, 
  * that device's scratch: calls that overlap in time on one device (other
  * streams, concurrent host threads) race and must not be issued.
  * Arguments, outputs and device errors: as murmur_decode_step.  Errors as
- * murmur_decode_step, plus MURMUR_ENOSPACE when the call's tickets and
- * partials (murmur_decode_attn_workspace for the same sizes and split_len)
- * exceed MURMUR_STATIC_SCRATCH_BYTES, and MURMUR_EHIP when the scratch's
+ * murmur_decode_step with a workspace of MURMUR_STATIC_SCRATCH_BYTES:
+ * MURMUR_ENOSPACE when the tickets and partials the call cannot do without
+ * (murmur_decode_attn_workspace) exceed it, and MURMUR_EHIP when the scratch's
  * address cannot be looked up. */
 #define MURMUR_STATIC_SCRATCH_BYTES (4u << 20)
 int murmur_decode_step_static(const murmur_seg *seg_dev, const murmur_policy *pol_dev, int32_t pol_per_seq,

@@ -80,19 +80,37 @@ int64_t lds_auto_split(int64_t max_keep, int64_t groups) {
     return std::max<int64_t>(len, 2 * kSplitUnit);
 }
 
-// The split length of grids beyond one dispatch round, whose sequences may be
-// of very different lengths (0: one split each).  A sequence takes only the
-// splits it needs, so short ones stay whole and long ones are shared out; where
-// all are long, the cuts cost up to 1 % in partials and merges.  Measured (us,
-// whole -> 2048): 28 layers x 12 chunks, four layers dense, 129.6 -> 127.8; 14
-// layers x 24 chunks at all stages of their decode 377 -> 367; 28 layers x 12
-// chunks, all dense, 338 -> 342.  When all workgroups are resident at once (two
-// per compute unit) cutting adds a round: 28 layers x 4 chunks of 3400 120 ->
-// 133; only much longer sequences gain: 28 layers x 3 of 9000 to 27000 607 ->
-// 527.  At most kMaxAutoSplits splits, and 64 MiB of partials.
-int64_t long_split(int64_t max_keep, int64_t groups, int64_t G) {
+// The split length of grids beyond one dispatch round (0: one split each).  A
+// sequence takes only the splits it needs, so short ones stay whole and long ones
+// are shared out.  That pays where whole groups leave compute units idle at the
+// end, and costs the partials and merges where they do not.  Two cases pay over
+// everything measured (us a launch, whole -> cut at 2048):
+// * Little more than one dispatch round of groups, which some compute units get
+//   two of and most only one: from four times the split up to 320 groups (260
+//   groups of 8192 223 -> 185, 304 groups, ragged up to 10400, 242 -> 210)
+//   and from five times up to 352 (336 of 20000 607 -> 536, ragged up to 10700
+//   306 -> 277; of 8192 238 -> 235, but ragged up to 9300 176 -> 180).  At 384
+//   groups and more it is even or loses: 384 of 14000 436 -> 439, 432 of 10000
+//   331 -> 348, 480 of 9500 344 -> 365, 672 of 3200 171 -> 178, of 8192 425 ->
+//   443, 1344 of 3200 348 -> 353; ragged ones gain or lose up to 10 %.
+// * Policies per layer, the calls whose groups differ in length by design (some
+//   layers dense; four of 28 dense and the others at 850 below).  From 3072
+//   positions: 1344 groups to 3200 148 -> 138, to 8192 249 -> 210; 672 groups to
+//   3200 91 -> 77 (to 2600 82 -> 76, but 1344 groups, 21 dense, 242 -> 250).  When
+//   all workgroups are resident at once (two per compute unit) only from 8192:
+//   448 groups to 8192 104 -> 83, but to 4096 64 -> 66, eight dense 71 -> 76.
+//   With nearly all layers dense it costs as above: 21 of 28 to 3200 289 -> 298.
+// At most kMaxAutoSplits splits, and 64 MiB of partials.
+int64_t long_split(int64_t max_keep, int64_t groups, int64_t G, bool per_layer) {
     if (groups <= kRoundWorkgroups) return 0;
-    if (max_keep < (groups > 2 * kRoundWorkgroups ? 3 * kLongSplit / 2 : 4 * kLongSplit)) return 0;
+    int64_t from = 0;
+    if (per_layer)
+        from = groups > 2 * kRoundWorkgroups ? 3 * kLongSplit / 2 : 4 * kLongSplit;
+    else if (groups <= 5 * kRoundWorkgroups / 4)
+        from = 4 * kLongSplit;
+    else if (groups <= 11 * kRoundWorkgroups / 8)
+        from = 5 * kLongSplit;
+    if (from == 0 || max_keep < from) return 0;
     const int64_t least = ((max_keep + kMaxAutoSplits - 1) / kMaxAutoSplits + kWaveTile - 1) / kWaveTile * kWaveTile;
     const int64_t len = std::max<int64_t>(kLongSplit, least);
     const int64_t n = (max_keep + len - 1) / len;
@@ -103,7 +121,7 @@ int64_t long_split(int64_t max_keep, int64_t groups, int64_t G) {
 }  // namespace
 
 WorkspacePlan plan_workspace(int32_t n_layers, int32_t B, int32_t Hq, int32_t Hkv, int32_t max_keep,
-                             int32_t split_len, bool cut_long) {
+                             int32_t split_len, LongCut cut_long) {
     WorkspacePlan p{};
     const int64_t groups = (int64_t)n_layers * B * Hkv;
     const int64_t G = Hkv > 0 ? Hq / Hkv : 0;
@@ -157,7 +175,8 @@ WorkspacePlan plan_workspace(int32_t n_layers, int32_t B, int32_t Hq, int32_t Hk
     } else {
         if (split_len <= 0) {
             split_len = (int32_t)lds_auto_split(max_keep, groups);  // a whole compute unit each
-            const int64_t cut = cut_long ? long_split(max_keep, groups, G) : 0;
+            const int64_t cut =
+                cut_long == LongCut::kNone ? 0 : long_split(max_keep, groups, G, cut_long == LongCut::kPerLayer);
             if (cut > 0) split_len = (int32_t)cut;
         }
         p.split_len = split_len;
@@ -229,9 +248,10 @@ void bind_workspace(AttnLaunch &a, void *ws_dev, size_t ws_bytes) {
 // decode steps (everything but where the retained sets come from).  With
 // ws_dev NULL and static_ws set, the workspace is the library's scratch array
 // of ws_bytes (bound by the caller after these checks); otherwise ws_dev.
+// per_layer: the call has a policy per layer.
 int prepare_attn(const void *q_dev, const murmur_kv *kv, int32_t max_keep, int32_t B, int32_t Hq, int32_t Hkv,
                  int32_t D, float scale, int32_t split_len, void *out_dev, int32_t out_dtype, float *lse_dev,
-                 void *ws_dev, size_t ws_bytes, AttnLaunch &a, bool static_ws = false) {
+                 void *ws_dev, size_t ws_bytes, AttnLaunch &a, bool per_layer = false, bool static_ws = false) {
     if (!q_dev || !kv || !out_dev || (!ws_dev && !static_ws))
         return fail(MURMUR_EINVAL, "q_dev, kv, out_dev and ws_dev must not be NULL");
     if (!kv->k || !kv->v) return fail(MURMUR_EINVAL, "kv->k and kv->v must not be NULL");
@@ -261,8 +281,10 @@ int prepare_attn(const void *q_dev, const murmur_kv *kv, int32_t max_keep, int32
         return fail(MURMUR_EINVAL, "out_dev must be 16-byte and lse_dev 4-byte aligned");
     if (!aligned(ws_dev, 256)) return fail(MURMUR_EINVAL, "ws_dev must be 256-byte aligned");
 
-    WorkspacePlan plan = plan_workspace(kv->n_layers, B, Hq, Hkv, max_keep, split_len);
-    if (ws_bytes < plan.total) plan = plan_workspace(kv->n_layers, B, Hq, Hkv, max_keep, split_len, false);
+    WorkspacePlan plan = plan_workspace(kv->n_layers, B, Hq, Hkv, max_keep, split_len,
+                                        per_layer ? LongCut::kPerLayer : LongCut::kByLength);
+    if (ws_bytes < plan.total)  // the cut's partials do not fit: the groups stay whole
+        plan = plan_workspace(kv->n_layers, B, Hq, Hkv, max_keep, split_len, LongCut::kNone);
     if (ws_bytes < plan.total && static_ws)
         return fail(MURMUR_ENOSPACE, "this call needs %zu bytes of scratch; the allocation-free step has %zu "
                     "(use murmur_decode_step with a workspace)", plan.total, ws_bytes);
@@ -457,7 +479,7 @@ MURMUR_EXPORT int murmur_decode_attn_workspace(int32_t n_layers, int32_t B, int3
     if (Hq % Hkv != 0) return fail(MURMUR_EINVAL, "Hq (%d) must be a multiple of Hkv (%d)", Hq, Hkv);
     if (split_len < 0 || split_len % kWaveTile != 0)
         return fail(MURMUR_EINVAL, "split_len must be 0 or a positive multiple of %d (got %d)", kWaveTile, split_len);
-    *bytes = plan_workspace(n_layers, B, Hq, Hkv, max_keep, split_len).total;
+    *bytes = plan_workspace(n_layers, B, Hq, Hkv, max_keep, split_len, LongCut::kPerLayer).total;  // the largest
     return ok();
 }
 
@@ -508,7 +530,7 @@ int prepare_step(const murmur_seg *seg_dev, const murmur_policy *pol_dev, int32_
         return fail(MURMUR_EINVAL, "seg/pol/idx/count/ranges pointers must be 4-byte aligned");
     if ((int64_t)B * max_keep > ((int64_t)1 << 40)) return fail(MURMUR_EINVAL, "B * max_keep too large");
     const int rc = prepare_attn(q_dev, kv, max_keep, B, Hq, Hkv, D, scale, split_len, out_dev, out_dtype, lse_dev,
-                                ws_dev, ws_bytes, a, static_ws);
+                                ws_dev, ws_bytes, a, (pol_per_seq & MURMUR_POL_PER_LAYER) != 0, static_ws);
     if (rc != MURMUR_OK) return rc;
     a.src0 = reinterpret_cast<const int32_t *>(seg_dev);
     a.src1 = reinterpret_cast<const int32_t *>(pol_dev);
@@ -613,7 +635,7 @@ MURMUR_EXPORT int murmur_decode_step_ring(const murmur_seg *seg_dev, const murmu
     if ((int64_t)B * max_keep > ((int64_t)1 << 40)) return fail(MURMUR_EINVAL, "B * max_keep too large");
     AttnLaunch a;
     const int rc = prepare_attn(q_dev, kv, max_keep, B, Hq, Hkv, D, scale, split_len, out_dev, out_dtype, lse_dev,
-                                ws_dev, ws_bytes, a);
+                                ws_dev, ws_bytes, a, (pol_per_seq & MURMUR_POL_PER_LAYER) != 0);
     if (rc != MURMUR_OK) return rc;
     a.src0 = reinterpret_cast<const int32_t *>(seg_dev);
     a.src1 = reinterpret_cast<const int32_t *>(pol_dev);

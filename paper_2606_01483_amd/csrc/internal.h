@@ -120,12 +120,16 @@ constexpr int kTicketStride = 32;
 // partials.
 size_t ticket_region(size_t ws_bytes);
 
+// Whether an automatic split length cuts long sequences in grids of more than
+// one dispatch round too (see long_split, api.cpp): never (such a launch needs no
+// partials: for workspaces that cannot hold them), where the lengths alone say
+// so, or as for a call with policies per layer (wherever kByLength does, and
+// more).
+enum class LongCut { kNone, kByLength, kPerLayer };
+
 // Split choice and workspace layout; deterministic in its arguments.
-// cut_long: cut long sequences in grids of more than one dispatch round too
-// (without, such a launch needs no partials: for workspaces that cannot hold
-// them).
 WorkspacePlan plan_workspace(int32_t n_layers, int32_t B, int32_t Hq, int32_t Hkv, int32_t max_keep,
-                             int32_t split_len, bool cut_long = true);
+                             int32_t split_len, LongCut cut_long);
 
 // Kernel launchers (kernels.hip).  They return a hipError_t value as int.
 int launch_evict_compact(const murmur_seg *seg, const murmur_policy *pol, int32_t pol_per_seq, int32_t B,

@@ -310,7 +310,8 @@ def test_decode_step_static_rejects(over, step_kw, code):
 
 
 def test_decode_step_static_scratch_limit():
-    """What fits: the calls whose workspace (same sizes and split_len) is at most MURMUR_STATIC_SCRATCH_BYTES."""
+    """What fits: the calls whose workspace (same sizes and split_len) is at most MURMUR_STATIC_SCRATCH_BYTES, and
+    those that could do without the rest of it (test_launch_plan.py)."""
     limit = M.MURMUR_STATIC_SCRATCH_BYTES
     assert M.murmur_decode_attn_workspace(1, 12, 28, 4, 850, 0) <= limit        # 12 x 300 s chunks, eviction
     assert M.murmur_decode_attn_workspace(28, 12, 28, 4, 850, 0) <= limit       # 28 layers

@@ -186,3 +186,47 @@ def test_ring_with_per_layer_policies():
     final = wl.seg(steps - 1)
     assert np.array_equal(rb.k[0].view(torch.uint16).cpu().numpy(), OR.append_all(wl.k, final, n_so, cap, rows))
     assert np.array_equal(rb.v[0].view(torch.uint16).cpu().numpy(), OR.append_all(wl.v, final, n_so, cap, rows))
+
+
+def test_long_dense_layers_cut_and_whole():
+    """528 groups, two of 33 layers dense: with the workspace the query returns, the dense groups of more than 2048
+    positions are cut and merged; with 256 bytes, and in the allocation-free step's scratch, every group is whole.
+    All three against the oracle, and the retained sets bit for bit."""
+    nl, b = 33, 4
+    seg0 = np.array([[5, 2900, 2, 250], [9, 600, 0, 30], [0, 2000, 3, 44], [3, 2047, 0, 1]], dtype=np.int32)
+    pol = np.zeros((nl, b, 5), dtype=np.int32)
+    pol[:] = [300, 64, 2, 40, 1]
+    pol[1] = pol[32] = [OFF, 0, 0, OFF, 0]
+    wl = W.build("long_layers", 91, nl, seg0, pol, 1, planted=False)
+    db = DecodeBatch(wl, out_dtype=M.MURMUR_DTYPE_F32, steps=[0])
+    assert db.max_keep >= 3072 and db.ws_bytes > M.MURMUR_STATIC_SCRATCH_BYTES
+    layers = [0, 1, 17, 32]
+    ref, ref_lse, sets = oracle_layers(wl, 0, layers)
+    first = None
+    for name, ws_bytes in (("cut", db.ws_bytes), ("whole", 256), ("static", 0), ("cut again", db.ws_bytes)):
+        announce(f"33 layers, two dense, {name}")
+        db.out.fill_(float("nan"))
+        db.lse.fill_(float("nan"))
+        for t in db.sets[0]:
+            t.fill_(-7)
+        if name == "static":
+            M.murmur_decode_step_static(db.seg[0], db.pol, db.pol_mode, db.q[0], db.kv[0], *db.sets[0], db.max_keep,
+                                        db.B, db.Hq, db.Hkv, db.D, wl.scale, 0, db.out, db.out_dtype, db.lse)
+        else:
+            M.murmur_decode_step(db.seg[0], db.pol, db.pol_mode, db.q[0], db.kv[0], *db.sets[0], db.max_keep, db.B,
+                                 db.Hq, db.Hkv, db.D, wl.scale, 0, db.out, db.out_dtype, db.lse, db.ws, ws_bytes)
+        torch.cuda.synchronize()
+        assert M.murmur_device_error() == 0
+        y, lse = db.out.cpu().numpy(), db.lse.cpu().numpy()
+        assert np.all(np.isfinite(y))
+        assert rel_err_fp32(y[layers], ref) <= REL_TOL
+        assert lse_err(lse[layers], ref_lse) <= LSE_TOL
+        idx, cnt, _ = (t.cpu().numpy() for t in db.sets[0])
+        for layer, (ref_idx, ref_cnt) in zip(layers, sets):
+            rows = slice(layer * b, (layer + 1) * b)
+            assert np.array_equal(cnt[rows], ref_cnt)
+            width = ref_idx.shape[1]
+            assert np.array_equal(idx[rows, :width], ref_idx) and np.all(idx[rows, width:] == -1)
+        got = [t.cpu() for t in db.sets[0]]
+        first = first or got
+        assert all(torch.equal(a, b) for a, b in zip(first, got))
