@@ -1573,7 +1573,23 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_attn_lds_kernel(const i
     const bool bad_count = cnt_seq < 1 || cnt_seq > max_keep;
     const int cnt = cnt_seq < 0 ? 0 : (cnt_seq > max_keep ? max_keep : cnt_seq);
     const int r_begin = split * a.split_len;
-    if (split > 0 && r_begin >= cnt) return;  // the sequence ends before this split
+    // Per-layer policies: one retained set per layer, else layer 0's workgroups
+    // write the sequence's.
+    const bool writes_set = (kSrc == kSrcLayout || kSrc == kSrcRing) && g == 0 &&
+                            (layer == 0 || (pol_per_seq & MURMUR_POL_PER_LAYER));
+    const int set = (pol_per_seq & MURMUR_POL_PER_LAYER) ? lb : b;
+    if (split > 0 && r_begin >= cnt) {
+        // The sequence ends before this split, which then has only its share of
+        // the index list's padding to write.  (Left to the last split that has
+        // positions, it was in front of that one's ticket: 12 x 832 positions in
+        // lists of 120,000 took 20.7 us instead of 17.4.)
+        if (writes_set && a.idx_out) {
+            int32_t *row = a.idx_out + (int64_t)set * max_keep;
+            const int hi = min(r_begin + a.split_len, max_keep);
+            for (int r = r_begin + tid; r < hi; r += kWaves * 64) row[r] = -1;
+        }
+        return;
+    }
     const int r_end = min(r_begin + a.split_len, cnt);
 
     RangeTab tab;
@@ -1649,11 +1665,8 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_attn_lds_kernel(const i
     // the merge.
     const int n = max(1, (cnt + a.split_len - 1) / a.split_len);
     write_result(a, o_lds, kStageWaveFloats, cl, bad, G, tid, row0, n == 1, (uint32_t)grp * a.n_split + split);
-    if ((kSrc == kSrcLayout || kRing) && g == 0 &&
-        (layer == 0 || (pol_per_seq & MURMUR_POL_PER_LAYER)))  // per-layer policies: one set per layer
-        write_retained<kWaves * 64>(a, (pol_per_seq & MURMUR_POL_PER_LAYER) ? layer * B + b : b, cnt_seq,
-                                         policy_bad, rg,
-                       max_keep, tid, r_begin, split == n - 1 ? max_keep : r_begin + a.split_len);
+    if (writes_set)
+        write_retained<kWaves * 64>(a, set, cnt_seq, policy_bad, rg, max_keep, tid, r_begin, r_begin + a.split_len);
     if (bad && tid == 0)
         raise_device_error((wg_bad_pos ? MURMUR_DEVERR_POSITION : 0) | (bad_count ? MURMUR_DEVERR_COUNT : 0));
     if (n == 1) return;

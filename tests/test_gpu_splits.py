@@ -63,6 +63,22 @@ def test_ragged_split_ends(split_len, layers):
     assert np.array_equal(db.idx.cpu().numpy(), idx[:, :db.max_keep])
 
 
+@pytest.mark.parametrize("split_len,layers", [(288, 1), (288, 4), (0, 1), (0, 8)])
+@pytest.mark.parametrize("max_keep", [1154, 2305, 9001])
+def test_index_list_longer_than_the_sequences(split_len, layers, max_keep):
+    """Lists of more entries than any sequence retains: the entries past each count are -1, whether its last split
+    or a split past its end covers them."""
+    from paper_2606_01483_amd.decode import DecodeBatch
+    wl = ragged(EDGES, layers)
+    db = DecodeBatch(wl, out_dtype=M.MURMUR_DTYPE_F32, steps=[0], split_len=split_len, max_keep=max_keep)
+    for t in db.sets[0]:
+        t.fill_(-7)
+    check(wl, db, lambda: db.step_fused(0), f"lists of {max_keep}, split_len {split_len}, {layers} layers")
+    idx, cnt = oracle.retained(wl.seg(0), wl.policy, max_keep)
+    assert np.array_equal(db.count.cpu().numpy(), cnt)
+    assert np.array_equal(db.idx.cpu().numpy(), idx)
+
+
 @pytest.mark.parametrize("hq,hkv", [(4, 4), (16, 1)])
 def test_ragged_split_ends_group_sizes(hq, hkv):
     from paper_2606_01483_amd.decode import DecodeBatch
