@@ -331,6 +331,8 @@ int prepare_attn(const void *q_dev, const murmur_kv *kv, int32_t max_keep, int32
     a.wide_wg = plan.wide_wg;
     a.sched = plan.sched;
     a.out_f32 = out_dtype == MURMUR_DTYPE_F32;
+    const int64_t row_bytes = (int64_t)B * a.Hkv * 2 * kHeadDim * 2;  // of one position of every sequence
+    a.stream_count = (int32_t)((kStreamBytes + row_bytes - 1) / row_bytes);
     a.scale_log2 = scale * 1.4426950408889634f;
     return ok();
 }

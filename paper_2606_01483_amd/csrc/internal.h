@@ -16,6 +16,23 @@ constexpr int kSplitUnit = 4 * kWaveTile;  // the LDS-staged schedule's split co
 constexpr int kMaxAutoSplits = 64;
 constexpr int kLongSplit = 2048;          // see long_split (api.cpp)
 constexpr int kRoundWorkgroups = 256;     // one workgroup per compute unit
+// K and V bytes of a layer's retained rows from which a launch streams them past
+// the L2s (kernels.hip, kAuxStream).  Below, the rows of all layers of a decoder
+// may fit the 256 MB Infinity Cache, and small ones the 32 MB of L2, so the next
+// token may find them there, and the normal policy is the faster one.  The line
+// is for a decoder of 28 layers; a launch cannot see how many there are, and where
+// fewer layers' caches stay in the Infinity Cache, streaming costs up to about
+// 30 MiB a layer.  A cache read again and again, a captured call per layer, us a
+// launch, normal -> streamed:
+//   850 rows a sequence:    8.3 MiB     10.0        13.3        19.9
+//     28 layers          6.56 -> 6.48  6.82 -> 6.72  7.52 -> 7.16  8.76 -> 8.30
+//     8 layers           6.29 -> 6.37  6.44 -> 6.51  6.84 -> 6.91  7.76 -> 7.88
+//     2 layers           5.64 -> 5.94  5.59 -> 5.95  5.69 -> 6.30  7.53 -> 7.16
+//   3482 rows a sequence:   6.8 MiB     13.6        20.4        34.0
+//     28 layers          6.90 -> 7.71  8.57 -> 8.27  8.82 -> 8.48  13.12 -> 12.25
+//     8 layers           6.84 -> 7.58  7.39 -> 7.85  8.20 -> 8.25  12.62 -> 12.02
+//     2 layers           6.43 -> 7.32  6.33 -> 7.52  8.23 -> 7.82  12.06 -> 11.34
+constexpr int64_t kStreamBytes = 12 << 20;
 // Splits one merge can combine: it stages 2 * n_split * G + 2 * G floats in
 // the workgroup's 32 KiB of V-tile LDS.
 constexpr int kMaxMergeSplits = 240;
@@ -95,6 +112,7 @@ struct AttnLaunch {
     uint32_t part_ml_bytes, part_o_bytes;  // extents of the two partial arrays (< 2^31)
     int32_t max_len, max_keep, B, Hq, Hkv, G, NL;
     int32_t split_len, n_split, out_f32;
+    int32_t stream_count;  // retained positions per sequence from which K/V rows are streamed (kStreamBytes)
     float scale_log2;  // logit scale times log2(e)
     int32_t wide_wg;   // > 0: the wide schedule with this many workgroups (sched)
     WideSched sched;

@@ -28,6 +28,7 @@
 #include <stdint.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "internal.h"
 #include "policy.h"
@@ -590,7 +591,7 @@ static __device__ __forceinline__ void wait_vm() {
 // not a matter of what the Infinity Cache keeps), 12 x 300 s with eviction
 // (21 MB) 8.68 -> 8.17 us, dense (78 MB) 19.7 -> 18.3, 28 layers x 12 chunks
 // in one launch (546 MB) 101.0 -> 88.4.  A small launch keeps the normal
-// policy (see stream_rows).
+// policy (kStreamBytes, internal.h).
 constexpr int kAuxStream = 2;  // nt
 
 // The 16 direct-to-LDS loads of one pass (8 for K, then 8 for V) into `stage`.
@@ -1623,37 +1624,45 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_attn_lds_kernel(const i
         materialize(tab.lo[1], tab.lo[2], tab.lo[3], tab.lo[4], tab.lo[5], tab.off[0], tab.off[1], tab.off[2],
                     tab.off[3], tab.off[4], tab.off[5]);
     const bool short_rows = a.s_pos < kRunRowLimit;
-    if (r < r_end) {
-        int32_t pos[8];
-        if (kSrc != kSrcIndex) {
-            dma_pass_ranges<kRing, kAux>(stage, tab, r, r_end, a.max_len, short_rows, kbase, vbase, a.s_pos, lane, c4,
-                                         w.bad_pos, nr);
-        } else {
-            dma_idx(ring[0], irow, r, lane);
-            dma_idx(ring[1], irow, r + kUnit, lane);
-            wait_vm<1>();
-            dma_pos_index(ring[0], r, r_end, a.max_len, c4, pos, w.bad_pos);
-            dma_pass<kAux>(stage, kbase, vbase, a.s_pos, pos, lane, kRing, nr);
-        }
-        for (int k = 0;; r += kUnit, ++k) {
-            wait_vm<0>();  // this pass's rows (and the next pass's entries)
-            PassOperands ops;
-            read_operands(ops, stage, n16, c4);
-            const bool more = r + kUnit < r_end;
-            if (more) {  // the next pass's rows into the stage just read
-                if (kSrc != kSrcIndex) {
-                    dma_pass_ranges<kRing, kAux>(stage, tab, r + kUnit, r_end, a.max_len, short_rows, kbase, vbase,
-                                                 a.s_pos, lane, c4, w.bad_pos, nr);
-                } else {
-                    dma_pos_index(ring[(k + 1) & 1], r + kUnit, r_end, a.max_len, c4, pos, w.bad_pos);
-                    dma_idx(ring[k & 1], irow, r + 2 * kUnit, lane);  // its slot is read
-                    dma_pass<kAux>(stage, kbase, vbase, a.s_pos, pos, lane, kRing, nr);
-                }
+    // The loads' cache policy, by the sequence's own count: max_keep, all that the
+    // launch knows, may be a bound far above it (one sequence of 832 positions with
+    // max_keep 9000, streamed 10.4 us, not 9.7).
+    const auto passes = [&](auto policy) {
+        constexpr int kPolicy = decltype(policy)::value;
+        if (r < r_end) {
+            int32_t pos[8];
+            if (kSrc != kSrcIndex) {
+                dma_pass_ranges<kRing, kPolicy>(stage, tab, r, r_end, a.max_len, short_rows, kbase, vbase, a.s_pos,
+                                                lane, c4, w.bad_pos, nr);
+            } else {
+                dma_idx(ring[0], irow, r, lane);
+                dma_idx(ring[1], irow, r + kUnit, lane);
+                wait_vm<1>();
+                dma_pos_index(ring[0], r, r_end, a.max_len, c4, pos, w.bad_pos);
+                dma_pass<kPolicy>(stage, kbase, vbase, a.s_pos, pos, lane, kRing, nr);
             }
-            compute_operands(ops, qf, min(kWaveTile, r_end - r), a.scale_log2, w, c4);
-            if (!more) break;
+            for (int k = 0;; r += kUnit, ++k) {
+                wait_vm<0>();  // this pass's rows (and the next pass's entries)
+                PassOperands ops;
+                read_operands(ops, stage, n16, c4);
+                const bool more = r + kUnit < r_end;
+                if (more) {  // the next pass's rows into the stage just read
+                    if (kSrc != kSrcIndex) {
+                        dma_pass_ranges<kRing, kPolicy>(stage, tab, r + kUnit, r_end, a.max_len, short_rows, kbase,
+                                                        vbase, a.s_pos, lane, c4, w.bad_pos, nr);
+                    } else {
+                        dma_pos_index(ring[(k + 1) & 1], r + kUnit, r_end, a.max_len, c4, pos, w.bad_pos);
+                        dma_idx(ring[k & 1], irow, r + 2 * kUnit, lane);  // its slot is read
+                        dma_pass<kPolicy>(stage, kbase, vbase, a.s_pos, pos, lane, kRing, nr);
+                    }
+                }
+                compute_operands(ops, qf, min(kWaveTile, r_end - r), a.scale_log2, w, c4);
+                if (!more) break;
+            }
         }
-    }
+    };
+    if (kAux == kAuxStream && cnt >= a.stream_count) passes(std::integral_constant<int, kAuxStream>{});
+    else passes(std::integral_constant<int, 0>{});
 
     if (kRing) store_new_row(a, app, nr, kbase, vbase, lane);
     float *o_lds = reinterpret_cast<float *>(&stages[0][0]);  // each wavefront's O rows in its own stage
@@ -2208,19 +2217,6 @@ static bool small_group_offsets(const AttnLaunch &a) {
     return last < ((__int128)1 << 31);
 }
 
-// Whether a launch streams its K/V rows past the L2s (see kAuxStream): when a
-// layer's retained rows come to at least kStreamBytes.  Below that, the rows of
-// all layers of a decoder may fit the 256 MB Infinity Cache, and small ones the
-// 32 MB of L2, so the next token may find them there, and then the normal
-// policy is the faster one.  One cache of 28 layers read again and again, us
-// per launch, normal / streamed: 0.4 MB a layer 4.56 / 5.21, 3.5 MB 5.92 /
-// 6.20, 7.0 MB 6.30 / 6.31, 11.4 MB 8.27 / 8.03, 14 MB 7.44 / 7.11; of 3 or 4
-// layers: 11.4 MB 8.12 / 8.86, 14 MB 7.92 / 7.90.
-constexpr double kStreamBytes = 12 << 20;
-static bool stream_rows(const AttnLaunch &a) {
-    return (double)a.B * a.Hkv * a.max_keep * (2 * kHeadDim * 2) >= kStreamBytes;
-}
-
 template <int kSrc, int kAux>
 static void launch_decode_attn_mode(const AttnLaunch &a, hipStream_t stream) {
     if (a.wide_wg > 0) {
@@ -2248,7 +2244,7 @@ static void launch_decode_attn_mode(const AttnLaunch &a, hipStream_t stream) {
 
 template <int kSrc>
 static void launch_decode_attn_src(const AttnLaunch &a, hipStream_t stream) {
-    if (stream_rows(a)) launch_decode_attn_mode<kSrc, kAuxStream>(a, stream);
+    if (a.max_keep >= a.stream_count) launch_decode_attn_mode<kSrc, kAuxStream>(a, stream);
     else launch_decode_attn_mode<kSrc, 0>(a, stream);
 }
 

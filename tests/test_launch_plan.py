@@ -68,7 +68,7 @@ int main() {  // lines: call mode layers batch Hq Hkv max_keep split_len ws_byte
         else if (!strcmp(call, "index"))
             rc = murmur_decode_attn(f, &kv, fi, nullptr, fi, keep, b, hq, hkv, 128, 1.f, split, f, 1, nullptr, f,
                                     bytes, nullptr);
-        printf("%d %d %d %zu\n", rc, got.n_split, got.split_len, need);
+        printf("%d %d %d %zu %d\n", rc, got.n_split, got.split_len, need, got.stream_count);
     }
     return 0;
 }
@@ -85,11 +85,13 @@ def plan(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", f"-I{ROOT}/include", f"-I{CSRC}", str(src),
                     os.path.join(CSRC, "api.cpp"), "-o", str(exe)], check=True, capture_output=True, text=True)
 
-    def run(call, mode, nl, b, keep, hq=28, hkv=4, split=0, ws=-1):
-        """(status, splits, split length, bytes the workspace query returns)"""
+    def run(call, mode, nl, b, keep, hq=28, hkv=4, split=0, ws=-1, stream=False):
+        """(status, splits, split length, bytes the workspace query returns), or with `stream` the retained count
+        from which a sequence's K/V rows are streamed"""
         line = f"{call} {mode} {nl} {b} {hq} {hkv} {keep} {split} {ws}\n"
         out = subprocess.run([str(exe)], input=line, capture_output=True, text=True, check=True).stdout
-        return tuple(int(x) for x in out.split())
+        got = tuple(int(x) for x in out.split())
+        return got[4] if stream else got[:4]
 
     return run
 
@@ -151,3 +153,12 @@ def test_explicit_splits_need_their_workspace(plan, call):
     rc, n, split, need = plan(call, PER_SEQ, 28, 12, 4096, split=2048)
     assert (rc, n, split) == (OK, 2, 2048)
     assert plan(call, PER_SEQ, 28, 12, 4096, split=2048, ws=need - 1)[0] == ENOSPACE
+
+
+@pytest.mark.parametrize("b,hkv,count", [(1, 4, 6144), (12, 4, 512), (64, 4, 96), (3, 1, 8192), (5, 4, 1229),
+                                         (65535, 4, 1)])
+def test_streaming_starts_at_twelve_mib_a_layer(plan, b, hkv, count):
+    """The smallest count with b * hkv * count * 512 bytes of K and V at 12 MiB or more."""
+    assert -(-(12 << 20) // (b * hkv * 512)) == count
+    for call in ("step", "ring", "ranges", "index"):
+        assert plan(call, 0, 1, b, 100, hq=hkv, hkv=hkv, stream=True) == count
