@@ -365,7 +365,7 @@ static __device__ __forceinline__ float sum_over_c4(float x) {
 }
 
 // Running softmax state of one wavefront for one (layer, sequence, KV head):
-// lane (head n16, c4) holds the max (log2 units) of head n16 and the sum over the
+// lane (head n16, c4) holds the max (unscaled) of head n16 and the sum over the
 // ranks it holds itself (a quarter of them); acc[db][i] is that head's O at head
 // dim 16*db + 4*c4 + i.
 struct WaveAcc {
@@ -392,6 +392,18 @@ static __device__ __forceinline__ void load_q(u32x4 (&qf)[4], const uint16_t *q,
     const uint16_t *qrow = q + (row_of_head0 + hq) * kHeadDim + 8 * c4;
 #pragma unroll
     for (int kc = 0; kc < 4; ++kc) qf[kc] = load16(qrow + kc * 32);
+}
+
+// The scale of the softmax, kept positive by its sign (and by 0) in the queries:
+// a negative or zero scale_log2 negates or clears them, which the products see
+// exactly.  Returns |scale_log2|, or 1 for 0.
+static __device__ __forceinline__ float signed_scale(u32x4 (&qf)[4], float scale_log2) {
+    const uint32_t bits = __builtin_bit_cast(uint32_t, scale_log2), mag = bits & 0x7fffffffu;
+    if (__builtin_expect((int32_t)bits <= 0, 0)) {  // uniform
+#pragma unroll
+        for (int kc = 0; kc < 4; ++kc) qf[kc] = mag ? qf[kc] ^ 0x80008000u : u32x4{0u, 0u, 0u, 0u};
+    }
+    return __builtin_bit_cast(float, mag ? mag : 0x3f800000u);
 }
 
 // The six-piece range table in cumulative form: rank r belongs to the last
@@ -458,80 +470,47 @@ static __device__ __forceinline__ void materialize(const T &...x) {
 // known to be empty.
 //
 // Bound by instruction issue (see decode_attn_lds_kernel), so what a pass does
-// not need is left out: the scale goes into the exponent's multiply-add; the sum
-// stays per lane (over its own ranks) until the state is published; and while no
-// head's max rises nothing is rescaled and no lane exchange is needed.  The
-// running max follows every rise: letting it lag by up to 4 saved 0.6 % on 12 x
-// 300 s dense and 1.4 % on 16 chunks from range tables, but then the largest
-// weight takes the rounding of hi + lo too (28 layers with planted keys: 1.9e-6
-// off, not 1.3e-6).
+// not need is left out: the sum stays per lane (over its own ranks) until the
+// state is published; while no head's max rises nothing is rescaled and no lane
+// exchange is needed.  The running max follows every rise: letting it lag by up
+// to 4 saved 0.6 % on 12 x 300 s dense and 1.4 % on 16 chunks from range tables,
+// but then the largest weight takes the rounding of hi + lo too (28 layers with
+// planted keys: 1.9e-6 off, not 1.3e-6).
 //
-// The max is a rounded product and the multiply-add subtracts it from the exact
-// one, so the largest weight is not exactly one but 2^d, |d| at most half a unit
-// in the last place of the max: 2^-9 below kMaxFused, where its distance from one
-// still lies in the lo part.  Far above, it would lose lo's bits (at 2^26 |d| is
-// 2) and from 2^31 overflow or vanish, so a head with such a max subtracts
-// rounded products, whose error is of the same order.  Which of the two a weight
-// takes depends on the running max of its own head alone, not on whether its pass
-// is whole or on the other heads: equal logits weigh the same in every pass.
-constexpr float kMaxFused = 0x1p16f;
+// The max is kept unscaled and subtracted before the scale is applied, so the
+// largest weight is exactly one whatever the logits' magnitude, and equal logits
+// weigh the same in every pass.  (The scale in a multiply-add on the rounded max
+// saves an instruction a weight, but then the largest weight is 2^d with |d| up
+// to half a unit in the last place of the max: 1.4e-3 off at logits of 2^16, out
+// of range from 2^31, and passes that round differently disagree by that much.)
+// scale > 0 (see signed_scale).
 template <bool kOnline>
-static __device__ __forceinline__ void softmax_step(const f32x4 (&s_all)[2], int valid, float scale_log2, WaveAcc &w,
+static __device__ __forceinline__ void softmax_step(const f32x4 (&s_all)[2], int valid, float scale, WaveAcc &w,
                                                     int c4, u32x4 &p_hi, u32x4 &p_lo) {
-    // One path for whole and partial passes, and everything else out of its way:
-    // a launch of one pass pays for each line of code it fetches (a second copy
-    // for partial passes cost 0.05 us of 4.5).
     f32x4 s[2] = {s_all[0], s_all[1]};
-    const auto in_pass = [valid, c4](int blk, int i) { return 16 * blk + 4 * c4 + i < valid; };
-    if (valid < kWaveTile) {
+    if (valid < kWaveTile) {  // uniform
 #pragma unroll
         for (int blk = 0; blk < 2; ++blk)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) s[blk][i] = in_pass(blk, i) ? s[blk][i] : kNegInf;
+            for (int i = 0; i < 4; ++i) s[blk][i] = 16 * blk + 4 * c4 + i < valid ? s[blk][i] : kNegInf;
     }
-    const bool positive = scale_log2 > 0.f;  // uniform; a masked logit is -inf then
-    float lane_max;                          // of this lane's logits, log2 units
-    if (__builtin_expect(positive, 1)) {
-        lane_max = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])),
-                         fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3]))) *
-                   scale_log2;
-    } else {
-        lane_max = kNegInf;
-#pragma unroll
-        for (int blk = 0; blk < 2; ++blk)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                lane_max = fmaxf(lane_max, in_pass(blk, i) ? s[blk][i] * scale_log2 : kNegInf);
-    }
+    const float lane_max = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])),
+                                 fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3])));
     if (!kOnline) {
         w.m_run = max_over_c4(lane_max);
     } else if (__ballot(lane_max > w.m_run)) {
         const float m_new = fmaxf(w.m_run, max_over_c4(lane_max));
-        const float alpha = __builtin_amdgcn_exp2f(w.m_run - m_new);  // 0 while the state is empty
+        const float alpha = __builtin_amdgcn_exp2f((w.m_run - m_new) * scale);  // 0 while the state is empty
         w.l_run *= alpha;
 #pragma unroll
         for (int db = 0; db < 8; ++db) w.acc[db] *= alpha;
         w.m_run = m_new;
     }
     float pr[2][4];
-    const bool far = fabsf(w.m_run) > kMaxFused;
-    if (__builtin_expect(positive && !__ballot(far), 1)) {
 #pragma unroll
-        for (int blk = 0; blk < 2; ++blk)
+    for (int blk = 0; blk < 2; ++blk)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                pr[blk][i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[blk][i], scale_log2, -w.m_run));
-    } else {
-#pragma unroll
-        for (int blk = 0; blk < 2; ++blk)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-#pragma clang fp contract(off)
-                const float x = s[blk][i] * scale_log2;
-                const float e = far ? x - w.m_run : __builtin_fmaf(s[blk][i], scale_log2, -w.m_run);
-                pr[blk][i] = __builtin_amdgcn_exp2f(in_pass(blk, i) ? e : kNegInf);
-            }
-    }
+        for (int i = 0; i < 4; ++i) pr[blk][i] = __builtin_amdgcn_exp2f((s[blk][i] - w.m_run) * scale);
     const float psum = ((pr[0][0] + pr[0][1]) + (pr[0][2] + pr[0][3])) + ((pr[1][0] + pr[1][1]) + (pr[1][2] + pr[1][3]));
     w.l_run = kOnline ? w.l_run + psum : psum;
 #pragma unroll
@@ -768,7 +747,7 @@ static __device__ __forceinline__ void dma_pos_index(const uint8_t *slot, int r0
 // (dma_pass: the K tile's, then the V tile's, the last loads this wavefront
 // issued) may still be in flight: the K operands are read once the K loads are
 // in, and S^T and the softmax are computed while the V loads land.
-static __device__ __forceinline__ void compute_pass_wide(const uint8_t *stage, const u32x4 (&qf)[4], int valid,
+static __device__ __forceinline__ void compute_pass_wide(const uint8_t *stage, u32x4 (&qf)[4], int valid,
                                                          float scale_log2, WaveAcc &w, int n16, int c4) {
     const uint32_t kt = lds_addr(stage), vt = kt + kTileBytes;
     // K operand (blk, kc): row 16*blk + n16, chunk 4*kc + c4 (row & 15 == n16);
@@ -801,6 +780,7 @@ static __device__ __forceinline__ void compute_pass_wide(const uint8_t *stage, c
           "=&v"(kf[7])
         : "v"(ka[0]), "v"(ka[1]), "v"(ka[2]), "v"(ka[3])
         : "memory");
+    const float scale = signed_scale(qf, scale_log2);
     f32x4 s[2];
 #pragma unroll
     for (int blk = 0; blk < 2; ++blk) {
@@ -809,7 +789,8 @@ static __device__ __forceinline__ void compute_pass_wide(const uint8_t *stage, c
         for (int kc = 0; kc < 4; ++kc) s[blk] = mfma16x16x32(kf[4 * blk + kc], qf[kc], s[blk]);
     }
     u32x4 p_hi, p_lo;
-    softmax_step<false>(s, valid, scale_log2, w, c4, p_hi, p_lo);
+    softmax_step<false>(s, valid, scale, w, c4, p_hi, p_lo);
+    w.m_run *= scale;  // the state's one pass: log2 units from here
     wait_vm<0>();  // the V tile's loads
     asm volatile(
         "ds_read_b64_tr_b16 %0, %16\n\t"
@@ -898,7 +879,7 @@ static __device__ __forceinline__ void read_operands(PassOperands &ops, const ui
         : "memory");
 }
 static __device__ __forceinline__ void compute_operands(const PassOperands &ops, const u32x4 (&qf)[4], int valid,
-                                                        float scale_log2, WaveAcc &w, int c4) {
+                                                        float scale, WaveAcc &w, int c4) {
     f32x4 s[2];
 #pragma unroll
     for (int blk = 0; blk < 2; ++blk) {
@@ -907,7 +888,7 @@ static __device__ __forceinline__ void compute_operands(const PassOperands &ops,
         for (int kc = 0; kc < 4; ++kc) s[blk] = mfma16x16x32(ops.kf[4 * blk + kc], qf[kc], s[blk]);
     }
     u32x4 p_hi, p_lo;
-    softmax_step<true>(s, valid, scale_log2, w, c4, p_hi, p_lo);
+    softmax_step<true>(s, valid, scale, w, c4, p_hi, p_lo);
 #pragma unroll
     for (int db = 0; db < 8; ++db) {
         const u32x4 av = u32x4{ops.vf[2 * db][0], ops.vf[2 * db][1], ops.vf[2 * db + 1][0], ops.vf[2 * db + 1][1]};
@@ -1627,6 +1608,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_attn_lds_kernel(const i
     // The loads' cache policy, by the sequence's own count: max_keep, all that the
     // launch knows, may be a bound far above it (one sequence of 832 positions with
     // max_keep 9000, streamed 10.4 us, not 9.7).
+    const float scale = signed_scale(qf, a.scale_log2);
     const auto passes = [&](auto policy) {
         constexpr int kPolicy = decltype(policy)::value;
         if (r < r_end) {
@@ -1656,7 +1638,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_attn_lds_kernel(const i
                         dma_pass<kPolicy>(stage, kbase, vbase, a.s_pos, pos, lane, kRing, nr);
                     }
                 }
-                compute_operands(ops, qf, min(kWaveTile, r_end - r), a.scale_log2, w, c4);
+                compute_operands(ops, qf, min(kWaveTile, r_end - r), scale, w, c4);
                 if (!more) break;
             }
         }
@@ -1664,6 +1646,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_attn_lds_kernel(const i
     if (kAux == kAuxStream && cnt >= a.stream_count) passes(std::integral_constant<int, kAuxStream>{});
     else passes(std::integral_constant<int, 0>{});
 
+    w.m_run *= scale;  // log2 units from here
     if (kRing) store_new_row(a, app, nr, kbase, vbase, lane);
     float *o_lds = reinterpret_cast<float *>(&stages[0][0]);  // each wavefront's O rows in its own stage
     constexpr int kStageWaveFloats = kStageBytes / 4;
