@@ -1982,6 +1982,7 @@ __global__ __launch_bounds__(kWideThreads) void decode_attn_wide_kernel(
                 a.ticket, a.part_ml, a.part_o, a.part_ml_bytes, a.part_o_bytes, a.out_f32);
     if (kSrc == kSrcLayout || kSrc == kSrcRing) materialize(a.idx_out, a.count_out, a.ranges_out);
     if (kSrc == kSrcRing) materialize(a.ring_cap, a.k_new, a.v_new);
+    if (kAux == kAuxStream && kSrc != kSrcIndex) materialize(a.stream_count);
     // Index lists: this pass's entries, before the count arrives (their ranks do
     // not depend on it, and the list has max_keep of them whatever the count):
     // behind the count they were a second round trip in front of the first K/V
@@ -2037,9 +2038,17 @@ __global__ __launch_bounds__(kWideThreads) void decode_attn_wide_kernel(
         const int valid = min(kWaveTile, r_end - r0);
         u32x4 qf[4];
         load_q(qf, q, row0, G, n16, c4);
+        // Range sources stream by the sequence's own count, as the LDS-staged kernel
+        // does (one sequence of 3132 positions with max_keep 9000, in splits of 250:
+        // 10.9 us streamed, 10.0 not).  Index lists don't: the choice cost 12 x 850
+        // paged positions 1.5 %.
         if (kSrc != kSrcIndex) {
-            dma_pass_ranges<kRing, kAux>(stage, tab, r0, r_end, a.max_len, short_rows, kbase, vbase, a.s_pos, lane, c4,
-                                   w.bad_pos, nr);
+            if (kAux == kAuxStream && cnt >= a.stream_count)
+                dma_pass_ranges<kRing, kAux>(stage, tab, r0, r_end, a.max_len, short_rows, kbase, vbase, a.s_pos, lane,
+                                             c4, w.bad_pos, nr);
+            else
+                dma_pass_ranges<kRing, 0>(stage, tab, r0, r_end, a.max_len, short_rows, kbase, vbase, a.s_pos, lane,
+                                          c4, w.bad_pos, nr);
         } else {
             int32_t pos[8];
             wait_vm<0>();  // the entries
