@@ -3,16 +3,19 @@
 kernels.hip is compiled by hipcc for gfx950 only; api.cpp (host-only C ABI
 layer) by g++.  The shared object lands next to this file, where the ctypes
 binding loads it, and beside it _pycall.so, the argument converter of the
-per-step calls (pycall.cpp).  Packed-fp32 instruction selection is disabled for device
-code, and the first 16 kernel-argument dwords are preloaded into SGPRs.  Only
-the murmur_* entry points are exported.
+per-step calls (pycall.cpp), where Python's headers are there to build it; the
+binding does without it.  Packed-fp32 instruction selection is disabled for
+device code, and the first 16 kernel-argument dwords are preloaded into SGPRs.
+Only the murmur_* entry points are exported.
 """
 from __future__ import annotations
 
+import glob
 import os
 import shutil
 import subprocess
 import sysconfig
+import warnings
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -43,6 +46,24 @@ KERNEL_FLAGS = [f"--offload-arch={ARCH}", *COMMON_FLAGS, "-Xclang", "-target-fea
                 "-mllvm", "-amdgpu-kernarg-preload-count=16"]
 
 
+def _build_pycall(verbose: bool) -> None:
+    """The argument converter.  None of an earlier build is left beside the new library, whose functions it would
+    call by the old signatures."""
+    for old in glob.glob(os.path.join(glob.escape(PKG), "_pycall*.so")):
+        os.remove(old)
+    tmp = PYCALL + ".tmp"
+    cmd = ["g++", *COMMON_FLAGS, "-Wextra", "-shared", f"-I{sysconfig.get_paths()['include']}",
+           os.path.join(CSRC, "pycall.cpp"), "-o", tmp]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    try:
+        _run(cmd)
+    except RuntimeError as e:
+        warnings.warn(f"the per-step calls will go through ctypes: {e}")
+        return
+    os.replace(tmp, PYCALL)
+
+
 def build(verbose: bool = False) -> str:
     """Compile every source and link libmurmur.so (always rebuilds)."""
     os.makedirs(BUILD_DIR, exist_ok=True)
@@ -63,13 +84,7 @@ def build(verbose: bool = False) -> str:
         print(" ".join(link), flush=True)
     _run(link)
     os.replace(tmp, LIB)
-    tmp = PYCALL + ".tmp"
-    cmd = ["g++", *COMMON_FLAGS, "-Wextra", "-shared", f"-I{sysconfig.get_paths()['include']}",
-           os.path.join(CSRC, "pycall.cpp"), "-o", tmp]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    _run(cmd)
-    os.replace(tmp, PYCALL)
+    _build_pycall(verbose)
     return LIB
 
 
