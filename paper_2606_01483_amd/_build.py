@@ -2,7 +2,7 @@
 
 kernels.hip is compiled by hipcc for gfx950 only; api.cpp (host-only C ABI
 layer) by g++.  The shared object lands next to this file, where the ctypes
-binding loads it, and beside it _pycall.so, the argument converter of the
+binding loads it, and beside it the _pycall module, the argument converter of the
 per-step calls (pycall.cpp), where Python's headers are there to build it; the
 binding does without it.  Packed-fp32 instruction selection is disabled for
 device code, and the first 16 kernel-argument dwords are preloaded into SGPRs.
@@ -22,7 +22,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libmurmur.so")
-PYCALL = os.path.join(PKG, "_pycall.so")
+PYCALL = os.path.join(PKG, "_pycall" + sysconfig.get_config_var("EXT_SUFFIX"))  # for this interpreter only
 BUILD_DIR = os.path.join(ROOT, "_build")
 ARCH = "gfx950"
 

@@ -1,6 +1,7 @@
 """The Python binding's per-step calls on both of their routes, the C argument converter (csrc/pycall.cpp) and ctypes,
 and the converter's build (no GPU: every call here fails at its checks or at the first HIP call, so the module is
 skipped where a GPU is visible)."""
+import importlib.machinery
 import os
 import warnings
 
@@ -51,3 +52,11 @@ def test_build_without_the_converter(monkeypatch, tmp_path):
         warnings.simplefilter("error")
         _build.build()
     assert (tmp_path / os.path.basename(_build.PYCALL)).read_text() == "built"
+
+
+def test_the_converter_is_for_one_interpreter():
+    """Its file carries this interpreter's tag, so another Python version does not load it and goes through ctypes."""
+    name = os.path.basename(_build.PYCALL)
+    suffixes = importlib.machinery.EXTENSION_SUFFIXES
+    assert name == "_pycall" + suffixes[0]
+    assert suffixes[0] not in (".so", ".abi3.so")
