@@ -16,6 +16,8 @@
 namespace {
 
 PyObject *g_data_ptr;  // "data_ptr"
+// murmur.py's classes of the two structures (structures(), called once when it is imported)
+PyTypeObject *g_kv_type, *g_ring_type;
 
 // One argument: get() is false when the object is not taken (with or without
 // an exception set).
@@ -42,17 +44,18 @@ struct Arg<T *> {  // device or host address: None, an int, or an object with da
     }
 };
 
-template <typename T>
-struct StructArg {  // a ctypes structure, by its buffer
+template <typename T, PyTypeObject *&type>
+struct StructArg {  // None, or the ctypes structure itself, by its buffer
     Py_buffer b{};
     const T *v = nullptr;
     bool get(PyObject *o) {
         if (o == Py_None) return true;
+        if (!type || !PyObject_TypeCheck(o, type)) return false;
         if (PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) != 0) {
             PyErr_Clear();
             return false;
         }
-        if (b.len != (Py_ssize_t)sizeof(T)) return false;
+        if (b.len < (Py_ssize_t)sizeof(T)) return false;
         v = static_cast<const T *>(b.buf);
         return true;
     }
@@ -61,9 +64,9 @@ struct StructArg {  // a ctypes structure, by its buffer
     }
 };
 template <>
-struct Arg<const murmur_kv *> : StructArg<murmur_kv> {};
+struct Arg<const murmur_kv *> : StructArg<murmur_kv, g_kv_type> {};
 template <>
-struct Arg<const murmur_ring *> : StructArg<murmur_ring> {};
+struct Arg<const murmur_ring *> : StructArg<murmur_ring, g_ring_type> {};
 
 template <>
 struct Arg<int32_t> {
@@ -135,10 +138,24 @@ ENTRY(decode_step_static)
 ENTRY(decode_step_ring)
 ENTRY(paged_step)
 
+PyObject *structures(PyObject *, PyObject *const *args, Py_ssize_t n) {
+    if (n != 2 || !PyType_Check(args[0]) || !PyType_Check(args[1])) {
+        PyErr_SetString(PyExc_TypeError, "structures: the classes of murmur_kv and murmur_ring");
+        return nullptr;
+    }
+    Py_INCREF(args[0]);
+    Py_INCREF(args[1]);
+    Py_XDECREF(g_kv_type);
+    Py_XDECREF(g_ring_type);
+    g_kv_type = reinterpret_cast<PyTypeObject *>(args[0]);
+    g_ring_type = reinterpret_cast<PyTypeObject *>(args[1]);
+    Py_RETURN_NONE;
+}
+
 #define METHOD(name) {#name, (PyCFunction)(void (*)(void))name, METH_FASTCALL, nullptr}
 PyMethodDef g_methods[] = {METHOD(evict_compact),      METHOD(evict_compact_paged), METHOD(decode_attn),
                            METHOD(decode_step),        METHOD(decode_step_static),  METHOD(decode_step_ring),
-                           METHOD(paged_step),         {nullptr, nullptr, 0, nullptr}};
+                           METHOD(paged_step),         METHOD(structures),          {nullptr, nullptr, 0, nullptr}};
 PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_pycall", nullptr, -1, g_methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

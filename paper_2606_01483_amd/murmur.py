@@ -63,7 +63,8 @@ _PER_STEP = ("evict_compact", "evict_compact_paged", "decode_attn", "decode_step
              "decode_step_ring", "paged_step")
 try:
     from . import _pycall
-except ImportError:
+    _pycall.structures(murmur_kv, murmur_ring)
+except (ImportError, AttributeError):  # not built, or a build of another version
     _pycall = None
 
 
