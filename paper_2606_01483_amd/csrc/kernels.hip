@@ -1654,8 +1654,8 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_attn_lds_kernel(const i
     const int wg_bad_pos = barrier_or<kWaves>(w.bad_pos, s_wave_flag, wave, lane);
     const bool bad = wg_bad_pos || bad_count;
     // Splits the sequence has: those past its end have left, and take no part in
-    // the merge.
-    const int n = max(1, (cnt + a.split_len - 1) / a.split_len);
+    // the merge.  (A split length may be anything up to 2^31 - 32.)
+    const int n = cnt > 0 ? (cnt - 1) / a.split_len + 1 : 1;
     write_result(a, o_lds, kStageWaveFloats, cl, bad, G, tid, row0, n == 1, (uint32_t)grp * a.n_split + split);
     if (writes_set)
         write_retained<kWaves * 64>(a, set, cnt_seq, policy_bad, rg, max_keep, tid, r_begin, r_begin + a.split_len);

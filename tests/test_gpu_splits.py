@@ -63,6 +63,20 @@ def test_ragged_split_ends(split_len, layers):
     assert np.array_equal(db.idx.cpu().numpy(), idx[:, :db.max_keep])
 
 
+@pytest.mark.parametrize("split_len", [1184, 2**30, 2**31 - 32])
+def test_one_long_split(split_len):
+    """Split lengths from just above the longest sequence to the largest that is accepted: every group whole."""
+    from paper_2606_01483_amd.decode import DecodeBatch
+    wl = ragged(EDGES, 1)
+    db = DecodeBatch(wl, out_dtype=M.MURMUR_DTYPE_F32, steps=[0], split_len=split_len)
+    assert db.ws_bytes == 256
+    for t in db.sets[0]:
+        t.fill_(-7)
+    idx, cnt = check(wl, db, lambda: db.step_fused(0), f"split_len {split_len}")
+    assert np.array_equal(db.count.cpu().numpy(), cnt)
+    assert np.array_equal(db.idx.cpu().numpy(), idx[:, :db.max_keep])
+
+
 @pytest.mark.parametrize("split_len,layers", [(288, 1), (288, 4), (0, 1), (0, 8)])
 @pytest.mark.parametrize("max_keep", [1154, 2305, 9001])
 def test_index_list_longer_than_the_sequences(split_len, layers, max_keep):
@@ -89,8 +103,9 @@ def test_ragged_split_ends_group_sizes(hq, hkv):
 
 @pytest.mark.parametrize("split_len", [0, 96, 288])
 def test_ring_passes_around_the_current_row(split_len):
-    """Ring storage: passes that hold the current token's row (whose K/V come with the call) beside passes that
-    take consecutive rows, with rings of exactly the window and the current row at their start, middle and end."""
+    """Ring storage of 2 MiB a layer, where every pass addresses its rows one by one: rings of exactly the window,
+    the current token's row (whose K/V come with the call) at their start, middle and end.  Streamed launches, which
+    take consecutive rows beside it, are test_gpu_ring.py's."""
     from paper_2606_01483_amd.decode import RingBatch
     cap = 40
     seg0 = np.array([[5, 300, 0, 40 + d] for d in (0, 1, 7, 31, 38, 39)], dtype=np.int32)
