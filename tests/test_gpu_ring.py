@@ -182,3 +182,89 @@ def test_ring_graph_replays_match_eager():
         torch.cuda.synchronize()
         assert torch.equal(rb.out, want_out)
         assert torch.equal(rb.k[0], want_k)
+
+
+# Sequences of streamed ring steps: (speech tokens, output tokens, output window), 3 prompt tokens and 4 output sinks,
+# a ring of 300.  The current token's row is, in ranks of the retained set: the last of a whole pass of 32 with the
+# next pass starting on the row after it (0), the first of a pass (1), inside one (2) and the ring's first row (3) of
+# windows that wrap; the last rank of the set as the last of a whole pass (4), alone in the last pass (5) and last of
+# a partial pass (6, 7), in rings that are not full; and two sequences short enough not to be streamed (8, 9).
+STREAMED = [(1017, 700, 300), (1018, 700, 300), (1001, 700, 300), (1000, 605, 300), (1000, 213, OFF), (1000, 214, OFF),
+            (1000, 224, OFF), (1000, 290, 100), (260, 700, 300), (300, 213, OFF)]
+
+
+def streamed_workload(n_layers):
+    seg0 = np.array([[3, s, 0, j - 1] for s, j, _ in STREAMED], dtype=np.int32)
+    pol = np.array([[OFF, 0, 0, w, 4] for _, _, w in STREAMED], dtype=np.int32)
+    return W.build("ring_streamed", 79, n_layers, seg0, pol, 1, planted=False)
+
+
+def test_streamed_sequences_cover_the_current_row():
+    """What STREAMED's comment says, from the host's layout of ring storage (passes from rank 0, as every split length
+    that is a multiple of 32 has them)."""
+    wl = streamed_workload(1)
+    ranges, cur = M.murmur_ring_layout_host(wl.seg(0), wl.policy, 300, 1)
+    seen = []
+    for b in range(wl.batch):
+        rows = expand(ranges[b])
+        at, n = rows.index(int(cur[b])), len(rows)
+        lo = at // 32 * 32
+        part = rows[lo:min(lo + 32, n)]
+        run = part == list(range(part[0], part[0] + len(part)))
+        starts = [sum(int(x) for x in ranges[b][:k, 1]) for k in range(6)]
+        one_piece = not any(lo < s < lo + len(part) for s in starts)
+        assert run or not one_piece
+        seen.append((at - lo, len(part), one_piece, at == n - 1, n))
+    assert seen[0][:4] == (31, 32, True, False)   # and the next pass starts on the row after it, in one piece
+    assert seen[1][:2] == (0, 32) and seen[2][0] == 15
+    assert cur[3] == 1003 + 4
+    assert seen[4][:4] == (31, 32, True, True)
+    assert seen[5][:4] == (0, 1, True, True)
+    assert seen[6][0] == seen[6][1] - 1 and seen[6][2:4] == (True, True) and 1 < seen[6][1] < 32
+    assert seen[7][0] == seen[7][1] - 1 and seen[7][3]
+    count = (12 << 20) // (wl.batch * wl.hkv * 512) + 1
+    assert all(s[4] > count for s in seen[:8]) and all(s[4] < count for s in seen[8:])
+
+
+@pytest.mark.parametrize("split_len,n_layers", [(0, 1), (96, 1), (192, 1), (288, 1), (288, 2), (0, 7)])
+def test_ring_streamed_steps(split_len, n_layers):
+    """Launches of at least 12 MiB of K/V a layer, whose passes of consecutive rows skip the per-row addresses unless
+    they hold the current token's row: the wide kernel (automatic, 96, 192), the LDS-staged kernel of eight wavefronts
+    (288, one layer) and of four (288, two layers; whole groups, seven layers).  The current token's row in storage is
+    NaN before the call, so reading it instead of the token's own K and V shows; afterwards it holds the token, and
+    nothing else has changed."""
+    announce(f"ring streamed, split_len {split_len}, {n_layers} layers")
+    wl = streamed_workload(n_layers)
+    cap, seg, n_so = 300, wl.seg(0), wl.policy[:, 4]
+    k_st, v_st, rows = oracle_storage(wl, 0, cap)
+    _, cur = M.murmur_ring_layout_host(seg, wl.policy, cap, 1)
+    for b in range(wl.batch):
+        k_st[:, b, :, int(cur[b])] = W.BF16_NAN
+        v_st[:, b, :, int(cur[b])] = W.BF16_NAN
+    idx, cnt = oracle.retained(seg, wl.policy)
+    ref, ref_lse = oracle.attend(wl.q(0), wl.k, wl.v, idx, cnt, scale=wl.scale, n_threads=16)
+    rb = RingBatch(wl, cap, out_dtype=M.MURMUR_DTYPE_F32, split_len=split_len, steps=[0], storage=(k_st, v_st))
+    assert rb.max_keep * wl.batch * wl.hkv * 512 >= 12 << 20
+    before = rb.k[0].clone(), rb.v[0].clone()
+    for again in range(3):
+        for x, x0 in zip((rb.k[0], rb.v[0]), before):
+            x.copy_(x0)
+        rb.out.fill_(float("nan"))
+        rb.idx.fill_(-7)
+        rb.step(0)
+        torch.cuda.synchronize()
+        assert M.murmur_device_error() == 0
+        y = rb.out.cpu().numpy()
+        assert np.all(np.isfinite(y))
+        assert rel_err_fp32(y, ref) <= REL_TOL
+        assert lse_err(rb.lse.cpu().numpy(), ref_lse) <= LSE_TOL
+        want_rows = OR.storage_rows(idx, cnt, seg, n_so, cap)
+        g_idx = rb.idx.cpu().numpy()
+        for b in range(wl.batch):
+            assert sorted(g_idx[b, :cnt[b]].tolist()) == sorted(want_rows[b]) and np.all(g_idx[b, cnt[b]:] == -1)
+        for got, x0, seq in ((rb.k[0], before[0], wl.k), (rb.v[0], before[1], wl.v)):
+            want = x0.clone()
+            for b in range(wl.batch):
+                token = torch.from_numpy(seq[:, b, :, int(seg[b].sum()) - 1].copy()).view(torch.bfloat16).cuda()
+                want[:, b, :, int(cur[b])] = token
+            assert torch.equal(got.view(torch.int16), want.view(torch.int16))
