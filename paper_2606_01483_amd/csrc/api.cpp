@@ -66,8 +66,8 @@ double wide_cost(int64_t len, int64_t n, int64_t G) {
 
 // The LDS-staged kernel's automatic split length: as many splits as keep one
 // dispatch round (fewer when there are more groups than that, at most
-// kMaxAutoSplits), counted in whole workgroup passes, then each split made as
-// short as that count allows in whole wavefront passes: a split's time is
+// kMaxAutoSplits), counted in units of kSplitUnit positions, then each split made
+// as short as that count allows in whole wavefront passes: a split's time is
 // bound by its compute unit's read rate, so rows past the longest sequence's
 // share only cost (12 x 300 s dense: 768 -> 704 positions, five splits either way).
 int64_t lds_auto_split(int64_t max_keep, int64_t groups) {

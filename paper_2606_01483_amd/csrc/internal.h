@@ -12,7 +12,10 @@ namespace murmur {
 constexpr int kHeadDim = 128;     // head_dim supported by the attention kernel
 constexpr int kMaxGroup = 16;     // query heads per KV head (MFMA tile height)
 constexpr int kWaveTile = 32;     // retained positions one wavefront handles per pass
-constexpr int kSplitUnit = 4 * kWaveTile;  // the LDS-staged schedule's split counts are chosen in units of 128 positions
+// The LDS-staged schedule's automatic split counts are chosen in units of 128
+// positions: a pass of its four-wavefront workgroup, half a pass of the
+// eight-wavefront one that runs them within one dispatch round.
+constexpr int kSplitUnit = 4 * kWaveTile;
 constexpr int kMaxAutoSplits = 64;
 constexpr int kLongSplit = 2048;          // see long_split (api.cpp)
 constexpr int kRoundWorkgroups = 256;     // one workgroup per compute unit
@@ -33,8 +36,8 @@ constexpr int kRoundWorkgroups = 256;     // one workgroup per compute unit
 //     8 layers           6.84 -> 7.58  7.39 -> 7.85  8.20 -> 8.25  12.62 -> 12.02
 //     2 layers           6.43 -> 7.32  6.33 -> 7.52  8.23 -> 7.82  12.06 -> 11.34
 constexpr int64_t kStreamBytes = 12 << 20;
-// Splits one merge can combine: it stages 2 * n_split * G + 2 * G floats in
-// the workgroup's 32 KiB of V-tile LDS.
+// Splits one merge can combine: it stages their 2 * n_split * G floats (30 KiB)
+// in the workgroup's K/V stages (64 KiB at least).
 constexpr int kMaxMergeSplits = 240;
 constexpr int kMaxKeep = 1 << 28;  // retained positions per sequence the attention accepts
 constexpr int kMergeBatch = 8;  // splits whose partials one merging thread loads at once

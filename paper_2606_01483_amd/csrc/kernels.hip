@@ -1605,10 +1605,10 @@ __global__ __launch_bounds__(kWaves * 64, 2) void decode_attn_lds_kernel(const i
         materialize(tab.lo[1], tab.lo[2], tab.lo[3], tab.lo[4], tab.lo[5], tab.off[0], tab.off[1], tab.off[2],
                     tab.off[3], tab.off[4], tab.off[5]);
     const bool short_rows = a.s_pos < kRunRowLimit;
+    const float scale = signed_scale(qf, a.scale_log2);
     // The loads' cache policy, by the sequence's own count: max_keep, all that the
     // launch knows, may be a bound far above it (one sequence of 832 positions with
-    // max_keep 9000, streamed 10.4 us, not 9.7).
-    const float scale = signed_scale(qf, a.scale_log2);
+    // max_keep 120,000: streamed 11.6 us, not 8.9).
     const auto passes = [&](auto policy) {
         constexpr int kPolicy = decltype(policy)::value;
         if (r < r_end) {
@@ -1949,6 +1949,7 @@ __global__ __launch_bounds__(kWideThreads) void decode_attn_wide_kernel(
     __shared__ CombineLdsT<kWideWaves> cl;
     __shared__ int s_last;
     __shared__ int s_wave_flag[kWideWaves];
+    static_assert(kOWaveBytes <= kStageBytes, "published rows fit a stage");
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;

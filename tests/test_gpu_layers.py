@@ -230,3 +230,32 @@ def test_long_dense_layers_cut_and_whole():
         got = [t.cpu() for t in db.sets[0]]
         first = first or got
         assert all(torch.equal(a, b) for a, b in zip(first, got))
+
+
+@pytest.mark.parametrize("split", ["cut", "whole"])
+def test_long_groups_cut_a_little_beyond_one_round(split):
+    """260 groups of one policy with a sequence of 8301 positions: cut into up to five splits where the workspace
+    holds the partials, each sequence by its own count, else whole."""
+    seg0 = np.array([[5, 8000, 0, 295], [3, 4090, 1, 1], [0, 2000, 0, 47], [9, 90, 0, 2], [2, 6000, 0, 200]],
+                    dtype=np.int32)
+    wl = W.build("long_groups", 92, 13, seg0, np.array([OFF, 0, 0, OFF, 0]), 1, planted=False)
+    db = DecodeBatch(wl, out_dtype=M.MURMUR_DTYPE_F32, steps=[0])
+    assert db.max_keep >= 8192 and db.ws_bytes > 256
+    if split == "whole":
+        db.ws_bytes = 256
+    idx, cnt = oracle.retained(wl.seg(0), wl.policy, db.max_keep)
+    layers = [0, 12]
+    ref, ref_lse = oracle.attend(wl.q(0)[layers], wl.k[layers], wl.v[layers], idx, cnt, scale=wl.scale, n_threads=16)
+    for again in range(2):
+        announce(f"260 groups, {split}, call {again}")
+        db.out.fill_(float("nan"))
+        for t in db.sets[0]:
+            t.fill_(-7)
+        db.step_fused(0)
+        torch.cuda.synchronize()
+        assert M.murmur_device_error() == 0
+        y = db.out.cpu().numpy()
+        assert np.all(np.isfinite(y))
+        assert rel_err_fp32(y[layers], ref) <= REL_TOL
+        assert lse_err(db.lse.cpu().numpy()[layers], ref_lse) <= LSE_TOL
+        assert np.array_equal(db.count.cpu().numpy(), cnt) and np.array_equal(db.idx.cpu().numpy(), idx)
