@@ -1506,7 +1506,7 @@ static __device__ __forceinline__ void merge_partials(const AttnLaunch &a, int n
 // for a pass, 0.7-1.1 us for its loads), so two wavefronts per SIMD share it:
 // with kWaves = 8 the workgroup takes a compute unit to itself (128 KiB; four
 // wavefronts with two stages each, one per SIMD, took 18.2 us on 12 x 300 s
-// dense and 16.4 us on 16 chunks from range tables, 17.7 and 15.0 now), and with
+// dense and 16.4 us on 16 chunks from range tables, 17.7 and 14.9 now), and with
 // kWaves = 4 (64 KiB, grids of more than one dispatch round) two workgroups do,
 // one's prologue, epilogue and dispatch gap overlapping the other's loads.
 // Index lists are staged too, one pass ahead of the rows.
